@@ -48,6 +48,7 @@ namespace revisit {
 namespace {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
@@ -57,6 +58,16 @@ constexpr float kLn2 = 0.6931471805599453f;
 // Accumulator row held by register i of a lane in wave half `hh` (32x32 MFMA).
 __device__ __forceinline__ int acc_row(int hh, int i) { return 8 * (i >> 2) + 4 * hh + (i & 3); }
 
+// max / sum of x over the lane and its partner in the other wave half
+__device__ __forceinline__ float half_swap_max(float x) {
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+}
+__device__ __forceinline__ float half_swap_sum(float x) {
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+
 struct BiasGeom {
     float gamma;  // lambda / (2 sigma^2 softmax_scale)
     float cx, cy;  // grid centre (w / 2, h / 2)
@@ -64,131 +75,272 @@ struct BiasGeom {
 };
 
 // ---------------------------------------------------------------------------
-// fp32 kernel: v_mfma_f32_32x32x2_f32. 4 waves x 32 queries per workgroup,
-// 32-key tiles staged in LDS.
+// fp32 kernel: v_mfma_f32_32x32x2_f32 (64 cycles each), so a 32-query,
+// 32-key tile keeps a SIMD's matrix core busy for 8192 cycles at D = 128
+// while it needs 32 KB of keys and values: bound by the matrix cores as long
+// as nothing waits. One workgroup takes 32 queries of one head; its kF32Waves
+// waves take every kF32Waves-th key tile each and work without a barrier
+// until they merge their results through LDS. That split leaves the chip's
+// last round of workgroups small (12 heads of 4680 queries are 1764 items,
+// 6.9 per compute unit, where 128-query items fill 444 of 512 places), and
+// gives a small problem eight waves per 32 queries.
+//
+// Operands come straight from global memory into registers, 16 bytes a lane.
+// The contraction index of an MFMA may be any numbering that both operands
+// share: step 4 g + i takes head dim 8 g + 4 hh + i, so a lane's operands of
+// four steps are 16 consecutive bytes of its key row, and four such loads
+// issued together cover whole 128-byte lines. The rows of V^T are numbered
+// the same way (row m of block db is head dim (D / 32) m + db), so one load
+// of a value row serves all blocks and the outputs of a lane are consecutive.
+// While the QK MFMAs use up the key registers the tile's values are loaded
+// into them, and the next tile's keys while PV uses up those: each load has
+// about half a tile's MFMAs (2 us) to land, in 64 registers. The queries, the
+// same for all waves, are read from LDS.
+//
+// Measured at H 12, D 128, Lq 4680, Lk 28080 (8.07e11 flops) with bias: 6.65 ms,
+// 121 TFLOP/s of the 154 that a large fp32 matrix product reaches here. The
+// kernel before it (128 queries per workgroup, tiles staged through registers
+// into LDS between two barriers, one 4-byte LDS read per MFMA) took 24.5 ms.
+// Four waves per item, two workgroups per compute unit: 7.48 ms. Lq 64, Lk 256,
+// D 64, one head: 8 us where the eight tiles took 54 us one after the other.
 // ---------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(256) void attn_f32_kernel(AttentionArgs a, BiasGeom g, float c_log2, bool bias_on) {
-    constexpr int TK = 32;
-    __shared__ float Ks[TK][D + 1];
-    __shared__ float Vs[TK][D];
+constexpr int kF32Waves = 8;
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int hh = lane >> 5;
-    const int n = lane & 31;
-    const int hd = blockIdx.y;
-    const int H = a.H;
-    const int q = blockIdx.x * 128 + wave * 32 + n;
-    const bool q_ok = q < a.Lq;
-    const float* Qg = static_cast<const float*>(a.q);
-    const float* Kg = static_cast<const float*>(a.k);
-    const float* Vg = static_cast<const float*>(a.v);
+// The correspondence of a lane's query in KV frame f.
+struct F32Corr {
+    int f;      // -1: none loaded yet
+    int valid;  // retrieved frame, accepted correspondence
+    float ux, uy;
+};
 
-    float qf[D / 2];
-#pragma unroll
-    for (int kk = 0; kk < D / 2; ++kk) qf[kk] = q_ok ? Qg[((size_t)q * H + hd) * D + 2 * kk + hh] : 0.0f;
-
-    floatx16 O[D / 32];
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db) O[db] = floatx16{0};
-    float m_run = -INFINITY, l_run = 0.0f;
-
-    for (int tile0 = 0; tile0 < a.Lk; tile0 += TK) {
-        __syncthreads();
-        for (int e = tid; e < TK * D; e += 256) {
-            const int r = e / D, c = e - (e / D) * D;
-            const int key = tile0 + r;
-            const bool in = key < a.Lk;
-            Ks[r][c] = in ? Kg[((size_t)key * H + hd) * D + c] : 0.0f;
-            Vs[r][c] = in ? Vg[((size_t)key * H + hd) * D + c] : 0.0f;
-        }
-        __syncthreads();
-
-        // the bias of this lane's 16 logits (query q, keys of rows acc_row(hh, i)),
-        // evaluated directly as -gamma ((u_k,x - u^_x)^2 + (u_k,y - u^_y)^2),
-        // differences first; it is the accumulator's start value
-        floatx16 acc = floatx16{0};
-        if (bias_on && q_ok) {
-            int cf = -1;  // frame whose query factors are loaded
-            bool valid = false;
-            float2 u = make_float2(0.0f, 0.0f);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int key = tile0 + acc_row(hh, i);
-                if (key >= a.Lk) continue;
-                const int f = key / g.hw;
-                if (f != cf) {
-                    cf = f;
-                    const int s = a.slot[f];
-                    valid = false;
-                    if (s >= 0 && s < a.S) {
-                        const size_t o = (size_t)s * a.Lq + q;
-                        if (a.corr_idx[o] >= 0) {
-                            valid = true;
-                            u = reinterpret_cast<const float2*>(a.corr_uv)[o];
-                        }
-                    }
-                }
-                if (valid) {
-                    const int t = key - f * g.hw;
-                    const int ky = t / g.w;
-                    const int kx = t - ky * g.w;
-                    const float dx = ((float)kx + 0.5f) - u.x;
-                    const float dy = ((float)ky + 0.5f) - u.y;
-                    acc[i] = -g.gamma * (dx * dx + dy * dy);
-                }
+// The bias of a lane's 16 logits (query q, keys of rows acc_row(hh, i) of the
+// tile at key k0), the accumulator's start value: evaluated directly as
+// -gamma ((u_k,x - u^_x)^2 + (u_k,y - u^_y)^2), differences first.
+__device__ __forceinline__ void f32_bias(floatx16& acc, F32Corr& c, const AttentionArgs& a, const BiasGeom& g, int k0,
+                                         int q, bool q_ok, int hh) {
+    const int span = min(32, a.Lk - k0);
+    const float inv_w = 1.0f / (float)g.w;
+    // frames that the tile touches, at in-frame key position t0 of its row 0 (negative past the first)
+    int f = k0 / g.hw;
+    int t0 = k0 - f * g.hw;
+    for (;;) {
+        if (f != c.f) {
+            c.f = f;
+            c.valid = 0;
+            const int s = __builtin_amdgcn_readfirstlane(a.slot[f]);
+            if (s >= 0 && s < a.S && q_ok) {
+                const size_t o = (size_t)s * a.Lq + q;
+                const float2 u = reinterpret_cast<const float2*>(a.corr_uv)[o];
+                c.valid = a.corr_idx[o] >= 0;
+                c.ux = u.x;
+                c.uy = u.y;
             }
         }
+        auto add = [&](auto row_of) __attribute__((always_inline)) {
 #pragma unroll
-        for (int kk = 0; kk < D / 2; ++kk) {
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(Ks[n][2 * kk + hh], qf[kk], acc, 0, 0, 0);
+            for (int i = 0; i < 16; ++i) {
+                const int t = t0 + acc_row(hh, i);
+                const int ky = row_of(t);
+                const int kx = t - ky * g.w;
+                const float dx = ((float)kx + 0.5f) - c.ux;
+                const float dy = ((float)ky + 0.5f) - c.uy;
+                if (c.valid && t >= 0 && t < g.hw) acc[i] = -g.gamma * (dx * dx + dy * dy);
+            }
+        };
+        if (__any(c.valid)) {
+            // (t + 1/2) / w truncates to t / w exactly below 2^20 keys per frame: its error is
+            // under t 2^-22 / w, its distance from a whole number at least 1 / (2 w)
+            if (g.hw <= (1 << 20)) add([&](int t) { return (int)(((float)t + 0.5f) * inv_w); });
+            else add([&](int t) { return t / g.w; });
+        }
+        if (t0 + span <= g.hw) break;  // the frame holds the tile's last key
+        ++f;
+        t0 -= g.hw;
+    }
+}
+
+template <int D>
+__global__ __launch_bounds__(64 * kF32Waves) void attn_f32_kernel(AttentionArgs a, BiasGeom g, float c_log2,
+                                                                  bool bias_on) {
+    constexpr int TK = 32;
+    constexpr int kG = D / 8;    // key vectors of a lane and tile
+    constexpr int kDb = D / 32;  // 32-dim blocks of the output
+    typedef float vvec __attribute__((ext_vector_type(kDb)));
+    __shared__ float lds_o[kF32Waves / 2][kDb * 16 * 64];
+    __shared__ float lds_m[kF32Waves][32], lds_l[kF32Waves][32];
+    __shared__ floatx4 lds_q[kG][64];  // the query vector of each lane, per four QK steps
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int hh = lane >> 5;
+    const int n = lane & 31;
+    // items head-major, each XCD a contiguous range: one head's keys and values meet in one L2
+    const int n_qt = (a.Lq + 31) / 32;
+    const unsigned n_items = (unsigned)n_qt * (unsigned)a.H;
+    const unsigned item = xcd_item(blockIdx.x, n_items);
+    if (item >= n_items) return;  // grid padding (uniform, before any barrier)
+    const int hd = (int)(item / (unsigned)n_qt);
+    const int q = (int)(item - (unsigned)hd * (unsigned)n_qt) * 32 + n;
+    const bool q_ok = q < a.Lq;
+    const int Lk = a.Lk;
+    const int n_tiles = (Lk + TK - 1) / TK;
+    const uint32_t row_bytes = (uint32_t)a.H * D * 4;  // at most 2^25
+    const uint8_t* Kg = static_cast<const uint8_t*>(a.k) + (size_t)hd * D * 4;
+    const uint8_t* Vg = static_cast<const uint8_t*>(a.v) + (size_t)hd * D * 4;
+
+    for (int j = wave; j < kG; j += kF32Waves) {
+        const float* Qg = static_cast<const float*>(a.q) + ((size_t)q * a.H + hd) * D + 4 * hh;
+        lds_q[j][lane] = q_ok ? *reinterpret_cast<const floatx4*>(Qg + 8 * j) : floatx4{0, 0, 0, 0};
+    }
+
+    floatx4 kf[kG];
+    vvec vf[16];
+    // key vector j of the lane's row (row n) of the tile at key k0; rows past Lk repeat the last one
+    auto k_off = [&](int k0) -> uint32_t { return (uint32_t)min(n, Lk - 1 - k0) * row_bytes + 16 * hh; };
+    auto load_k = [&](const uint8_t* base, uint32_t off, int j) {
+        kf[j] = *reinterpret_cast<const floatx4*>(base + off + 32 * j);
+    };
+    // value row of PV step kk: row acc_row(hh, kk) of the tile
+    const uint32_t v_off = (uint32_t)(4 * hh) * row_bytes + 4 * kDb * n;
+    auto load_v = [&](auto full_tag, const uint8_t* base, int k0, int kk) {
+        if constexpr (decltype(full_tag)::value) {
+            vf[kk] = *reinterpret_cast<const vvec*>(base + (size_t)acc_row(0, kk) * row_bytes + v_off);
+        } else {
+            const int r = acc_row(hh, kk);
+            vf[kk] = k0 + r < Lk ? *reinterpret_cast<const vvec*>(base + (size_t)((uint32_t)r * row_bytes + 4 * kDb * n)) : vvec{};
+        }
+    };
+
+    floatx16 O[kDb];
+#pragma unroll
+    for (int db = 0; db < kDb; ++db) O[db] = floatx16{0};
+    float m_run = -INFINITY, l_run = 0.0f;
+
+    F32Corr corr{-1, 0, 0.0f, 0.0f};
+
+    // one key tile (its keys are in kf) and the load of the wave's next one's keys
+    auto tile = [&](auto full_tag, int k0, int k_next) __attribute__((always_inline)) {
+        constexpr bool kFull = decltype(full_tag)::value;
+        const uint8_t* vb = Vg + (size_t)k0 * row_bytes;
+        floatx16 acc = floatx16{0};
+        if (bias_on) f32_bias(acc, corr, a, g, k0, q, q_ok, hh);
+        floatx4 qv = lds_q[0][lane];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < kG; ++j) {
+            const floatx4 qj = qv;
+            if (j + 1 < kG) qv = lds_q[j + 1][lane];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j][i], qj[i], acc, 0, 0, 0);
+#pragma unroll
+            for (int kk = j * 16 / kG; kk < (j + 1) * 16 / kG; ++kk) load_v(full_tag, vb, k0, kk);
+            __builtin_amdgcn_sched_barrier(0);
         }
 
-        // online softmax over this tile (column n = this lane's query)
+        // online softmax (column n = this lane's query, its other 16 keys in the other wave half)
         float mx = -INFINITY;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            if (tile0 + acc_row(hh, i) >= a.Lk) acc[i] = -INFINITY;
+            if (!kFull && k0 + acc_row(hh, i) >= Lk) acc[i] = -INFINITY;
             mx = fmaxf(mx, acc[i]);
         }
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
-        const float m_new = fmaxf(m_run, mx * c_log2);
-        const float alpha = exp2f(m_run - m_new);
+        mx = half_swap_max(mx) * c_log2;
+        if (__any(mx > m_run)) {
+            const float m_new = fmaxf(m_run, mx);
+            const float alpha = m_run == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m_run - m_new);
+            l_run *= alpha;
+#pragma unroll
+            for (int db = 0; db < kDb; ++db) O[db] *= alpha;
+            m_run = m_new;
+        }
+        const float m_sub = m_run == -INFINITY ? 0.0f : m_run;  // no finite logit so far: every weight is 0
         float lsum = 0.0f;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            acc[i] = exp2f(acc[i] * c_log2 - m_new);
+            acc[i] = __builtin_amdgcn_exp2f(fmaf(acc[i], c_log2, -m_sub));
             lsum += acc[i];
         }
-        l_run = l_run * alpha + lsum;
-        m_run = m_new;
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db) O[db] *= alpha;
+        l_run += lsum;
+        __builtin_amdgcn_sched_barrier(0);
 
         // O^T += V^T P^T: contraction step kk pairs accumulator register kk
         // (key acc_row(hh, kk)) in both operands
+        const uint8_t* kb = Kg + (size_t)k_next * row_bytes;
+        const uint32_t ko = k_off(k_next);
 #pragma unroll
         for (int kk = 0; kk < 16; ++kk) {
-            const int kr = acc_row(hh, kk);
 #pragma unroll
-            for (int db = 0; db < D / 32; ++db) {
-                O[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(Vs[kr][32 * db + n], acc[kk], O[db], 0, 0, 0);
+            for (int db = 0; db < kDb; ++db) O[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[kk][db], acc[kk], O[db], 0, 0, 0);
+            if (kk % 4 == 3) {
+#pragma unroll
+                for (int j = (kk / 4) * kG / 4; j < (kk / 4 + 1) * kG / 4; ++j) load_k(kb, ko, j);
             }
+            __builtin_amdgcn_sched_barrier(0);
         }
+    };
+
+    __syncthreads();  // lds_q
+    // this wave's tiles; past its last one the last tile's keys are loaded again and not used
+    if (wave < n_tiles) {
+        const uint8_t* kb = Kg + (size_t)(wave * TK) * row_bytes;
+        const uint32_t ko = k_off(wave * TK);
+#pragma unroll
+        for (int j = 0; j < kG; ++j) load_k(kb, ko, j);
+        int t = wave;
+        for (; (t + 1) * TK <= Lk; t += kF32Waves) {
+            tile(std::true_type{}, t * TK, min(t + kF32Waves, n_tiles - 1) * TK);
+        }
+        if (t < n_tiles) tile(std::false_type{}, t * TK, t * TK);
     }
 
-    const float l_tot = l_run + __shfl_xor(l_run, 32);
-    const float inv = 1.0f / l_tot;
-    if (q_ok) {
-        float* Og = static_cast<float*>(a.o) + ((size_t)q * H + hd) * D;
+    // merge: every wave scales its sums to the rows' common maximum, then the
+    // upper half of the remaining waves hands its sums to the lower half
+    float l_tot = half_swap_sum(l_run);
+    if (hh == 0) {
+        lds_m[wave][n] = m_run;
+        lds_l[wave][n] = l_tot;
+    }
+    __syncthreads();
+    float M = -INFINITY;
 #pragma unroll
-        for (int db = 0; db < D / 32; ++db) {
+    for (int w = 0; w < kF32Waves; ++w) M = fmaxf(M, lds_m[w][n]);
+    const float mine = m_run == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m_run - M);
 #pragma unroll
-            for (int i = 0; i < 16; ++i) Og[32 * db + acc_row(hh, i)] = O[db][i] * inv;
+    for (int db = 0; db < kDb; ++db) O[db] *= mine;
+    l_tot = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kF32Waves; ++w) {
+        const float mw = lds_m[w][n];
+        l_tot += mw == -INFINITY ? 0.0f : lds_l[w][n] * __builtin_amdgcn_exp2f(mw - M);
+    }
+#pragma unroll
+    for (int half = kF32Waves / 2; half >= 1; half /= 2) {
+        if (wave >= half && wave < 2 * half) {
+#pragma unroll
+            for (int db = 0; db < kDb; ++db)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) lds_o[wave - half][(db * 16 + i) * 64 + lane] = O[db][i];
         }
-        if (a.lse && hh == 0) a.lse[(size_t)hd * a.Lq + q] = (m_run + log2f(l_tot)) * kLn2;
+        __syncthreads();
+        if (wave < half) {
+#pragma unroll
+            for (int db = 0; db < kDb; ++db)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) O[db][i] += lds_o[wave][(db * 16 + i) * 64 + lane];
+        }
+        __syncthreads();
+    }
+    if (wave == 0 && q_ok) {
+        const float inv = 1.0f / l_tot;
+        float* Og = static_cast<float*>(a.o) + ((size_t)q * a.H + hd) * D;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            vvec o;
+#pragma unroll
+            for (int db = 0; db < kDb; ++db) o[db] = O[db][i] * inv;
+            *reinterpret_cast<vvec*>(Og + kDb * acc_row(hh, i)) = o;
+        }
+        if (a.lse && hh == 0) a.lse[(size_t)hd * a.Lq + q] = (M + log2f(l_tot)) * kLn2;
     }
 }
 
@@ -313,16 +465,6 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
     float r;
     asm volatile("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
     return r;
-}
-
-// max / sum of x over the lane and its partner in the other wave half
-__device__ __forceinline__ float half_swap_max(float x) {
-    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
-}
-__device__ __forceinline__ float half_swap_sum(float x) {
-    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
 }
 
 // Direct global -> LDS loads of one K or V tile of 32 rows. Wave `wave`
@@ -1107,7 +1249,7 @@ hipError_t launch_attention_f32(const AttentionArgs& a, hipStream_t stream) {
     if (a.Lq == 0) return hipSuccess;
     const BiasGeom g = make_geom(a);
     const bool bias_on = a.S > 0 && a.lambda != 0.0f;
-    const dim3 grid((a.Lq + 127) / 128, a.H), block(256);
+    const dim3 grid(xcd_grid((unsigned)((a.Lq + 31) / 32) * (unsigned)a.H)), block(64 * kF32Waves);
     const float c = a.softmax_scale * kLog2e;
     if (a.D == 64) {
         hipLaunchKernelGGL(attn_f32_kernel<64>, grid, block, 0, stream, a, g, c, bias_on);
