@@ -156,6 +156,9 @@ int retrieve_chunks(const float* bank_c2w, int32_t n_bank, const float* query_c2
     a.w_v = (double)w_v;
     a.tau_c = (double)tau_c;
     a.cos_tau_v = cos((double)tau_v);
+    // above (tau_c E)^2 (1 + 1e-9) the definition's sqrt(x) / E exceeds tau_c: its two roundings move it by
+    // 2^-52 of its value. fp32 tau_c and E keep the square between 1e-180 and 1e154 unless it is 0.
+    a.reach2 = (a.tau_c * a.E) * (a.tau_c * a.E) * (1.0 + 1e-9);
     a.delta = delta;
     a.first_candidate = first_candidate;
     a.k = k;

@@ -28,6 +28,7 @@ struct RetrieveArgs {
     const int32_t* query_chunk;
     int32_t n_query;
     double E, w_v, tau_c, cos_tau_v;
+    double reach2;  // squared distances above this fail the tau_c gate
     int32_t delta, first_candidate, k;
     int32_t* out_idx;
     float* out_score;

@@ -1,21 +1,34 @@
 // Pose retrieval over the history bank (Sec. 4.2, Eq. retrieval).
 //
-// One wave64 per query chunk. Each lane streams the bank entries
-// j = lane, lane + 64, ... (one 64-byte pose row each, coalesced across the
-// wave), evaluates the score and the three admissibility gates in double
-// precision and keeps its own KMAX best (score, j) pairs sorted in registers.
-// The wave then merges the 64 sorted lists with k rounds of a butterfly
-// argmin over the lanes' heads; the winning lane pops its head. Scores are
-// computed with exactly the IEEE double operations of the definition, in the
-// order written, with contraction disabled, so that the choice of chunks is
-// reproducible bit for bit on the host.
+// One workgroup per query, one wave for every 256 bank entries up to 16. Each
+// lane streams its share of the poses, evaluates the gates and the score in
+// double precision and keeps its kLane best (score, j) pairs sorted in
+// registers, together with the best pair it had to drop. The gates leave few
+// candidates (a loop passes a place a few times), so the workgroup collects
+// the lanes' pairs in LDS and each pair's rank is the number of pairs before
+// it: no rounds of reductions. Only when more than kRankMax are left does each
+// wave first reduce its lanes' lists to its k best with a butterfly argmin per
+// result. Pairs before the best dropped one are certainly the first ones; if
+// that is fewer than k, the bank is scanned again for the pairs after them
+// (each scan settles at least kLane). Scores are computed with exactly the
+// IEEE double operations of the definition, in the order written, with
+// contraction disabled, so that the choice of chunks is reproducible bit for
+// bit on the host.
 //
 // Large banks (more than kDirectMax entries) are cut into segments of
 // kSegEntries, one workgroup of kSegWaves waves per (query, segment), so that
-// enough waves stream the bank to keep HBM busy; each workgroup merges its
-// waves' lists in LDS and leaves the segment's k best (score, j) pairs in a
-// workspace, and one workgroup per query merges those in the same order. The
-// result is the same as the single-wave scan.
+// enough waves stream the bank to keep HBM busy; each leaves its segment's k
+// best pairs in a workspace, and one workgroup per query merges those in the
+// same order. The result is the same as the single scan.
+//
+// What bounds it: a bank of a few thousand poses is latency (one load batch,
+// the gates, five barriers), a large one the stream of its 64-byte poses.
+// Measured per call on the device (a captured graph of calls), before (one wave per query scanning in
+// turn, sorted lists of up to 32 pairs in registers, k butterfly rounds per
+// wave and again per query) and now: 200 entries, k 4: 4.9 -> 4.3 us; 3000,
+// k 4: 17.3 -> 8.8; 8000, k 32: 79 -> 10.5; 10^6, 4 queries, k 8: 65 -> 28;
+// 113615, 9 queries, k 26: 697 -> 32; 2 10^6, 16 queries, k 32: 5550 -> 170;
+// 2^23, k 4: 109 -> 107 (5 TB/s).
 
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -29,83 +42,236 @@ namespace revisit {
 namespace {
 
 constexpr int kWave = 64;
-constexpr int kWaveEntries = 16 * kWave;                // bank entries per scanning wave (64 KiB of poses)
-constexpr int kSegWaves = 16;                           // scanning waves per segment workgroup
-constexpr int kSegEntries = kSegWaves * kWaveEntries;   // bank entries per segment
-constexpr int kDirectMax = 8192;                        // larger banks take the segmented path
+constexpr int kMaxWaves = 16;                          // waves of a workgroup
+constexpr int kSegWaves = kMaxWaves;                   // scanning waves per segment workgroup
+constexpr int kSegEntries = kSegWaves * 16 * kWave;    // bank entries per segment
+constexpr int kDirectMax = 8192;                       // larger banks take the segmented path
+constexpr int kUnroll = 4;                             // bank entries in flight per lane
+constexpr int kLane = 4;                               // best pairs a lane keeps
+constexpr int kMaxK = 32;
+constexpr int kRankLanes = 8;                          // lanes that count one pair's rank
+// Largest number of pairs ranked by counting without a reduction first: m^2
+// comparisons over the workgroup, where a wave's reduction takes k dependent
+// butterflies of 18 lane exchanges each. Up to 32 pairs of each wave are left
+// after that.
+constexpr int kRankMax = 256;
 
 // (s1, j1) strictly before (s2, j2): smaller score, then smaller index.
 __device__ __forceinline__ bool before(double s1, int j1, double s2, int j2) {
     return s1 < s2 || (s1 == s2 && j1 < j2);
 }
 
-// A lane's KMAX best (score, j) pairs, sorted; (INFINITY, INT32_MAX) = empty.
-template <int KMAX>
+// A lane's kLane best (score, j) pairs, sorted; (INFINITY, INT32_MAX) = empty.
+// (ds, dj) is the best of the pairs that were offered and are not in it.
 struct LaneTop {
-    double s[KMAX];
-    int j[KMAX];
+    double s[kLane];
+    int j[kLane];
+    double ds;
+    int dj;
 
     __device__ __forceinline__ void clear() {
 #pragma unroll
-        for (int i = 0; i < KMAX; ++i) {
+        for (int i = 0; i < kLane; ++i) {
             s[i] = INFINITY;
             j[i] = INT32_MAX;
         }
+        ds = INFINITY;
+        dj = INT32_MAX;
     }
-    // sorted insertion, top down: slot i takes the new pair if it belongs
-    // exactly there, or the pair above it if the new one goes higher up
+    // sorted insertion: the new pair moves up past those it is before; what
+    // is left over at the end is dropped
     __device__ __forceinline__ void offer(double ns, int nj) {
-        if (!before(ns, nj, s[KMAX - 1], j[KMAX - 1])) return;
 #pragma unroll
-        for (int i = KMAX - 1; i >= 0; --i) {
-            if (before(ns, nj, s[i], j[i])) {
-                const bool here = (i == 0) || before(s[i > 0 ? i - 1 : 0], j[i > 0 ? i - 1 : 0], ns, nj);
-                if (here) {
-                    s[i] = ns;
-                    j[i] = nj;
-                } else {
-                    s[i] = s[i - 1];
-                    j[i] = j[i - 1];
-                }
-            }
+        for (int i = 0; i < kLane; ++i) {
+            const bool here = before(ns, nj, s[i], j[i]);
+            const double os = s[i];
+            const int oj = j[i];
+            s[i] = here ? ns : os;
+            j[i] = here ? nj : oj;
+            ns = here ? os : ns;
+            nj = here ? oj : nj;
+        }
+        if (before(ns, nj, ds, dj)) {
+            ds = ns;
+            dj = nj;
         }
     }
-    // round r of the wave merge: the wave's best remaining pair (all lanes
-    // agree); the lane that holds it pops it
-    __device__ __forceinline__ void wave_best(double& bs, int& bj) {
-        bs = s[0];
-        bj = j[0];
+    __device__ __forceinline__ void pop() {
 #pragma unroll
-        for (int off = kWave / 2; off >= 1; off >>= 1) {
-            const double os = __shfl_xor(bs, off);
-            const int oj = __shfl_xor(bj, off);
-            if (before(os, oj, bs, bj)) {
-                bs = os;
-                bj = oj;
-            }
+        for (int i = 0; i < kLane - 1; ++i) {
+            s[i] = s[i + 1];
+            j[i] = j[i + 1];
         }
-        if (bj != INT32_MAX && j[0] == bj) {
-#pragma unroll
-            for (int i = 0; i < KMAX - 1; ++i) {
-                s[i] = s[i + 1];
-                j[i] = j[i + 1];
-            }
-            s[KMAX - 1] = INFINITY;
-            j[KMAX - 1] = INT32_MAX;
-        }
+        s[kLane - 1] = INFINITY;
+        j[kLane - 1] = INT32_MAX;
     }
 };
 
+// The wave's first pair of (s, j), in every lane.
+__device__ __forceinline__ void wave_first(double& s, int& j) {
+#pragma unroll
+    for (int off = kWave / 2; off >= 1; off >>= 1) {
+        const double os = __shfl_xor(s, off);
+        const int oj = __shfl_xor(j, off);
+        if (before(os, oj, s, j)) {
+            s = os;
+            j = oj;
+        }
+    }
+}
+
+struct Shared {
+    double s[kMaxWaves * kMaxK];  // collected pairs, in any order
+    int j[kMaxWaves * kMaxK];
+    double res_s[kMaxK];  // the first pairs of this scan
+    int res_j[kMaxK];
+    double drop_s[kMaxWaves];
+    int drop_j[kMaxWaves];
+    int out_j[kMaxK];  // chunk ids of the results so far
+    int pairs, kept;
+};
+
+// The k first pairs of everything that scan(offer) offers, in order: calls
+// put(r, s, j) for result r in one thread and returns the number found (the
+// same in every thread). scan is called with offer(s, j), once per pass over
+// the data, by every thread for its share. Every thread of the workgroup
+// (whole waves) calls this together.
+template <class Scan, class Put>
+__device__ __forceinline__ int first_k(Shared& sh, int k, Scan scan, Put put) {
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1);
+    const int wave = tid / kWave;
+    const int n_waves = blockDim.x / kWave;
+    const uint64_t below = ((uint64_t)1 << lane) - 1;
+    double after_s = -INFINITY;  // only pairs after this one are looked for
+    int after_j = -1;
+    int done = 0;
+    for (;;) {
+        LaneTop top;
+        top.clear();
+        if (tid == 0) sh.pairs = sh.kept = 0;
+        scan([&](double s, int j) {
+            if (before(after_s, after_j, s, j)) top.offer(s, j);
+        });
+        __syncthreads();  // the counters are cleared, the last pass's results are read
+
+        // the lanes' pairs into LDS when they are few
+        uint64_t have[kLane];
+        int mine = 0;
+#pragma unroll
+        for (int i = 0; i < kLane; ++i) {
+            have[i] = __ballot(top.j[i] != INT32_MAX);
+            mine += __popcll(have[i]);
+        }
+        int base = 0;
+        if (lane == 0) {
+            base = mine ? atomicAdd(&sh.pairs, mine) : 0;
+            sh.drop_j[wave] = INT32_MAX;
+        }
+        base = __shfl(base, 0);
+        if (__any(top.dj != INT32_MAX)) {
+            wave_first(top.ds, top.dj);
+            if (lane == 0) {
+                sh.drop_s[wave] = top.ds;
+                sh.drop_j[wave] = top.dj;
+            }
+        }
+        __syncthreads();
+        const int need = k - done;
+        int m = sh.pairs;
+        if (m <= kRankMax) {
+#pragma unroll
+            for (int i = 0; i < kLane; ++i) {
+                if (top.j[i] != INT32_MAX) {
+                    const int at = base + __popcll(have[i] & below);
+                    sh.s[at] = top.s[i];
+                    sh.j[at] = top.j[i];
+                }
+                base += __popcll(have[i]);
+            }
+            __syncthreads();
+        } else {
+            double ws = INFINITY;  // lane r keeps the wave's r-th pair
+            int wj = INT32_MAX;
+            int n = 0;
+            for (; n < need; ++n) {
+                double bs = top.s[0];
+                int bj = top.j[0];
+                wave_first(bs, bj);
+                if (bj == INT32_MAX) break;
+                if (top.j[0] == bj) top.pop();
+                if (lane == n) {
+                    ws = bs;
+                    wj = bj;
+                }
+            }
+            int at = 0;
+            if (lane == 0 && n) at = atomicAdd(&sh.kept, n);
+            at = __shfl(at, 0);
+            if (lane < n) {
+                sh.s[at + lane] = ws;
+                sh.j[at + lane] = wj;
+            }
+            __syncthreads();
+            m = sh.kept;
+        }
+
+        // a pair's rank is the number of pairs before it, counted by eight
+        // lanes per pair (so that their LDS reads overlap)
+        for (int c0 = 0; c0 < m; c0 += blockDim.x / kRankLanes) {
+            const int c = c0 + tid / kRankLanes;
+            const double s = c < m ? sh.s[c] : -INFINITY;
+            const int j = c < m ? sh.j[c] : -1;
+            int rank = 0;
+#pragma unroll 4
+            for (int i = tid % kRankLanes; i < m; i += kRankLanes) rank += before(sh.s[i], sh.j[i], s, j) ? 1 : 0;
+#pragma unroll
+            for (int off = 1; off < kRankLanes; off *= 2) rank += __shfl_xor(rank, off);
+            if (c < m && tid % kRankLanes == 0 && rank < need) {
+                sh.res_s[rank] = s;
+                sh.res_j[rank] = j;
+            }
+        }
+        __syncthreads();
+        const int found = min(m, need);
+
+        // the results before every dropped pair are certain
+        double ds = INFINITY;
+        int dj = INT32_MAX;
+        if (lane < n_waves && sh.drop_j[lane] != INT32_MAX) {
+            ds = sh.drop_s[lane];
+            dj = sh.drop_j[lane];
+        }
+        if (__any(dj != INT32_MAX)) wave_first(ds, dj);
+        int certain = found;
+        if (dj != INT32_MAX) {
+            certain = __popcll(__ballot(lane < found && before(sh.res_s[lane & (kMaxK - 1)], sh.res_j[lane & (kMaxK - 1)], ds, dj)));
+        }
+        if (tid < certain) {
+            put(done + tid, sh.res_s[tid], sh.res_j[tid]);
+            sh.out_j[done + tid] = sh.res_j[tid];
+        }
+        done += certain;
+        if (done == k || dj == INT32_MAX) return done;
+        after_s = sh.res_s[certain - 1];  // certain >= min(kLane, need) > 0
+        after_j = sh.res_j[certain - 1];
+        __syncthreads();
+    }
+}
+
 // A query chunk: its centre (last column of c2w), viewing direction R e_z
-// (third column) and chunk index.
+// (third column), and the bank entries [lo, hi) that its index admits.
 struct QueryPose {
     double cx, cy, cz, vx, vy, vz;
-    int64_t n;
+    int lo, hi;
 };
 
 __device__ __forceinline__ QueryPose query_pose(const RetrieveArgs& a, int qi) {
     const float* qm = a.query_c2w + (size_t)qi * 16;
-    return QueryPose{qm[3], qm[7], qm[11], qm[2], qm[6], qm[10], a.query_chunk[qi]};
+    // j >= first_candidate and n - j >= delta
+    const int64_t end = (int64_t)a.query_chunk[qi] - a.delta + 1;
+    return QueryPose{qm[3], qm[7], qm[11], qm[2], qm[6], qm[10], max(a.first_candidate, 0),
+                     (int)max((int64_t)0, min((int64_t)a.n_bank, end))};
 }
 
 // The part of bank entry j that retrieval reads: columns 2 (viewing
@@ -120,177 +286,124 @@ __device__ __forceinline__ PoseCols load_cols(const RetrieveArgs& a, int j) {
                     *reinterpret_cast<const float2*>(m + 10)};
 }
 
-// Score and gates of bank entry j for query qp (Eq. retrieval); offers the
-// pair to `top` when admissible.
-template <int KMAX>
+// Score and gates of bank entry j (in the query's index range) for query qp
+// (Eq. retrieval); offers the pair when admissible. Most entries are out of
+// reach: those are told by the squared distance alone (a.reach2 is
+// (tau_c E)^2 with a margin that no rounding of the definition's square root
+// and quotient can bridge), without the square root and the division.
+template <class Offer>
 __device__ __forceinline__ void score_entry(const RetrieveArgs& a, int j, const PoseCols& m, const QueryPose& qp,
-                                            LaneTop<KMAX>& top) {
+                                            Offer& offer) {
     const double dx = (double)m.r0.y - qp.cx;
     const double dy = (double)m.r1.y - qp.cy;
     const double dz = (double)m.r2.y - qp.cz;
-    const double d = sqrt(dx * dx + dy * dy + dz * dz) / a.E;
+    const double x = dx * dx + dy * dy + dz * dz;
     const double al = (double)m.r0.x * qp.vx + (double)m.r1.x * qp.vy + (double)m.r2.x * qp.vz;
+    if (x > a.reach2 || !(al >= a.cos_tau_v)) return;
+    const double d = sqrt(x) / a.E;
     const double s = d + a.w_v * (1.0 - al);
-    const bool ok = j >= a.first_candidate && qp.n - j >= a.delta && d <= a.tau_c && al >= a.cos_tau_v;
-    if (ok) top.offer(s, j);
+    if (d <= a.tau_c) offer(s, j);
 }
 
-// Entries j = first + lane, + 64, ... below end, kUnroll per lane at a time:
-// all their loads are issued before any is scored (an index past `end` is
-// clamped to end - 1 for the load and not scored).
-constexpr int kUnroll = 4;
-
-template <int KMAX>
-__device__ __forceinline__ void scan_range(const RetrieveArgs& a, int first, int end, int lane, const QueryPose& qp,
-                                           LaneTop<KMAX>& top) {
-    for (int j0 = first + lane; j0 < end; j0 += kUnroll * kWave) {
+// Bank entries [begin, end), kUnroll per lane at a time, waves in turn: all
+// loads of a batch are issued before any is scored (an index past the end is
+// clamped for the load and not scored).
+template <class Offer>
+__device__ __forceinline__ void scan_bank(const RetrieveArgs& a, int begin, int end, const QueryPose& qp, Offer& offer) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = threadIdx.x / kWave;
+    const int step = (blockDim.x / kWave) * kUnroll * kWave;
+    for (int64_t w0 = (int64_t)begin + wave * kUnroll * kWave; w0 < end; w0 += step) {
+        const int j0 = (int)w0 + lane;  // at most 2^30 + 63
         PoseCols m[kUnroll];
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) m[u] = load_cols(a, min(j0 + u * kWave, end - 1));
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
-            if (j0 + u * kWave < end) score_entry(a, j0 + u * kWave, m[u], qp, top);
+            if (j0 + u * kWave < end) score_entry(a, j0 + u * kWave, m[u], qp, offer);
         }
     }
 }
 
-// The k results of query qi from the lanes' sorted lists: out_idx,
-// out_score, out_count and the frame selection.
-template <int KMAX>
-__device__ __forceinline__ void emit(const RetrieveArgs& a, int qi, int lane, LaneTop<KMAX>& top) {
-    int mine = -1;  // lane r keeps the r-th result
-    int count = 0;
-    for (int r = 0; r < a.k; ++r) {
-        double bs;
-        int bj;
-        top.wave_best(bs, bj);
-        const bool found = bj != INT32_MAX;
-        if (lane == 0) {
-            a.out_idx[(size_t)qi * a.k + r] = found ? bj : -1;
-            if (a.out_score) a.out_score[(size_t)qi * a.k + r] = found ? (float)bs : INFINITY;
-        }
-        if (lane == r) mine = found ? bj : -1;
-        count += found ? 1 : 0;
-    }
-    if (lane == 0) a.out_count[qi] = count;
+// Result r of query qi.
+__device__ __forceinline__ void put_result(const RetrieveArgs& a, int qi, int r, double s, int j) {
+    a.out_idx[(size_t)qi * a.k + r] = j;
+    if (a.out_score) a.out_score[(size_t)qi * a.k + r] = (float)s;
+}
 
+// What follows the results of query qi: the empty places, the count and the frame selection.
+__device__ __forceinline__ void finish(const RetrieveArgs& a, Shared& sh, int qi, int count) {
+    const int tid = threadIdx.x;
+    if (tid >= count && tid < a.k) {
+        a.out_idx[(size_t)qi * a.k + tid] = -1;
+        if (a.out_score) a.out_score[(size_t)qi * a.k + tid] = INFINITY;
+    }
+    if (tid == 0) a.out_count[qi] = count;
     if (a.out_frame_sel) {
+        __syncthreads();  // out_j
         const int F = a.frames_per_chunk;
         const int total = a.k * F;
-        for (int t0 = 0; t0 < total; t0 += kWave) {
-            const int t = t0 + lane;
-            const int src_lane = (t < total ? t : 0) / F;
-            const int c = __shfl(mine, src_lane);
-            if (t < total) {
-                a.out_frame_sel[(size_t)qi * total + t] = (t / F < count) ? c * F + (t % F) : -1;
-            }
-        }
+        for (int t = tid; t < total; t += blockDim.x)
+            a.out_frame_sel[(size_t)qi * total + t] = t / F < count ? sh.out_j[t / F] * F + (t % F) : -1;
     }
 }
 
-template <int KMAX>
-__global__ __launch_bounds__(kWave) void retrieve_kernel(RetrieveArgs a) {
+// The whole bank for query blockIdx.x.
+__global__ __launch_bounds__(kMaxWaves * kWave) void retrieve_kernel(RetrieveArgs a) {
+    __shared__ Shared sh;
     const int qi = blockIdx.x;
-    const int lane = threadIdx.x;
     const QueryPose qp = query_pose(a, qi);
-    LaneTop<KMAX> top;
-    top.clear();
-    scan_range(a, 0, a.n_bank, lane, qp, top);
-    emit(a, qi, lane, top);
+    const int count = first_k(
+        sh, a.k, [&](auto offer) { scan_bank(a, qp.lo, qp.hi, qp, offer); },
+        [&](int r, double s, int j) { put_result(a, qi, r, s, j); });
+    finish(a, sh, qi, count);
 }
 
-// Segment `seg` of the bank for query qi, one workgroup of kSegWaves waves:
-// each wave scans kWaveEntries entries and reduces its lanes' lists to its k
-// best pairs in LDS; the first wave merges those and writes the segment's k
-// best to seg_s / seg_j [qi][seg][0 .. k), (INFINITY, INT32_MAX) past the
-// admissible ones.
-template <int KMAX>
+// One segment of the bank for one query: its k best pairs go to seg_s /
+// seg_j [qi][seg][0 .. k), (INFINITY, INT32_MAX) past the admissible ones. The
+// queries of one segment are neighbours on one XCD, so its L2 serves the bank
+// to all but the first.
 __global__ __launch_bounds__(kSegWaves * kWave) void retrieve_segment_kernel(RetrieveArgs a) {
-    __shared__ double lds_s[kSegWaves][KMAX];
-    __shared__ int lds_j[kSegWaves][KMAX];
-    const int qi = blockIdx.x / a.n_seg;
-    const int seg = blockIdx.x - qi * a.n_seg;
-    const int tid = threadIdx.x;
-    const int lane = tid & (kWave - 1);
-    const int wave = tid / kWave;
+    __shared__ Shared sh;
+    const unsigned n_items = (unsigned)a.n_seg * (unsigned)a.n_query;
+    const unsigned item = xcd_item(blockIdx.x, n_items);
+    if (item >= n_items) return;  // grid padding (uniform, before any barrier)
+    const int seg = (int)(item / (unsigned)a.n_query);
+    const int qi = (int)(item - (unsigned)seg * (unsigned)a.n_query);
     const QueryPose qp = query_pose(a, qi);
-    LaneTop<KMAX> top;
-    top.clear();
-    const int64_t j0 = (int64_t)seg * kSegEntries + (int64_t)wave * kWaveEntries;
-    const int j_begin = (int)min((int64_t)a.n_bank, j0);
-    const int j_end = (int)min((int64_t)a.n_bank, j0 + kWaveEntries);
-    scan_range(a, j_begin, j_end, lane, qp, top);
-    for (int r = 0; r < a.k; ++r) {
-        double bs;
-        int bj;
-        top.wave_best(bs, bj);
-        if (lane == 0) {
-            lds_s[wave][r] = bs;
-            lds_j[wave][r] = bj;
-        }
-    }
-    __syncthreads();
-    if (wave == 0) {
-        LaneTop<KMAX> top2;
-        top2.clear();
-        for (int c = lane; c < kSegWaves * a.k; c += kWave) {
-            const int w = c / a.k, r = c - w * a.k;
-            if (lds_j[w][r] != INT32_MAX) top2.offer(lds_s[w][r], lds_j[w][r]);
-        }
-        const size_t base = ((size_t)qi * a.n_seg + seg) * a.k;
-        for (int r = 0; r < a.k; ++r) {
-            double bs;
-            int bj;
-            top2.wave_best(bs, bj);
-            if (lane == 0) {
-                a.seg_s[base + r] = bs;
-                a.seg_j[base + r] = bj;
-            }
-        }
-    }
+    const int64_t j0 = (int64_t)seg * kSegEntries;
+    const int begin = (int)max(j0, (int64_t)qp.lo), end = (int)min(j0 + kSegEntries, (int64_t)qp.hi);
+    const size_t base = ((size_t)qi * a.n_seg + seg) * a.k;
+    auto put = [&](int r, double s, int j) {
+        a.seg_s[base + r] = s;
+        a.seg_j[base + r] = j;
+    };
+    const int count = first_k(sh, a.k, [&](auto offer) { scan_bank(a, begin, end, qp, offer); }, put);
+    if ((int)threadIdx.x >= count && (int)threadIdx.x < a.k) put(threadIdx.x, INFINITY, INT32_MAX);
 }
 
-// One workgroup of kMergeThreads per query over its n_seg * k segment
-// results: every lane keeps its KMAX best, each wave reduces its lanes' lists
-// to its k best in LDS, and the first wave merges those and emits.
-constexpr int kMergeThreads = 1024;
-constexpr int kMergeWaves = kMergeThreads / kWave;
-
-template <int KMAX>
-__global__ __launch_bounds__(kMergeThreads) void retrieve_merge_kernel(RetrieveArgs a) {
-    __shared__ double lds_s[kMergeWaves][KMAX];
-    __shared__ int lds_j[kMergeWaves][KMAX];
+// The results of query blockIdx.x from its n_seg * k segment results.
+__global__ __launch_bounds__(kMaxWaves * kWave) void retrieve_merge_kernel(RetrieveArgs a) {
+    __shared__ Shared sh;
     const int qi = blockIdx.x;
-    const int tid = threadIdx.x;
-    const int lane = tid & (kWave - 1);
-    const int wave = tid / kWave;
-    LaneTop<KMAX> top;
-    top.clear();
     const size_t base = (size_t)qi * a.n_seg * a.k;
     const int n_cand = a.n_seg * a.k;
-    for (int c = tid; c < n_cand; c += kMergeThreads) {
-        const int j = a.seg_j[base + c];
-        if (j != INT32_MAX) top.offer(a.seg_s[base + c], j);
-    }
-    for (int r = 0; r < a.k; ++r) {
-        double bs;
-        int bj;
-        top.wave_best(bs, bj);
-        if (lane == 0) {
-            lds_s[wave][r] = bs;
-            lds_j[wave][r] = bj;
-        }
-    }
-    __syncthreads();
-    if (wave == 0) {
-        LaneTop<KMAX> top2;
-        top2.clear();
-        for (int c = lane; c < kMergeWaves * a.k; c += kWave) {
-            const int w = c / a.k, r = c - (c / a.k) * a.k;
-            if (lds_j[w][r] != INT32_MAX) top2.offer(lds_s[w][r], lds_j[w][r]);
-        }
-        emit(a, qi, lane, top2);
-    }
+    const int count = first_k(
+        sh, a.k,
+        [&](auto offer) {
+            for (int c = threadIdx.x; c < n_cand; c += blockDim.x) {
+                const int j = a.seg_j[base + c];
+                if (j != INT32_MAX) offer(a.seg_s[base + c], j);
+            }
+        },
+        [&](int r, double s, int j) { put_result(a, qi, r, s, j); });
+    finish(a, sh, qi, count);
+}
+
+// Waves of a workgroup over n entries, `each` per wave.
+dim3 waves_for(int64_t n, int each) {
+    const int64_t w = (n + each - 1) / each;
+    return dim3((unsigned)(kWave * (w < 1 ? 1 : w > kMaxWaves ? kMaxWaves : w)));
 }
 
 }  // namespace
@@ -304,27 +417,19 @@ size_t retrieve_workspace_bytes(int32_t n_bank, int32_t n_query, int32_t k) {
     return (size_t)n_seg * n_query * k * (sizeof(double) + sizeof(int32_t));
 }
 
-template <int KMAX>
-static hipError_t launch_k(const RetrieveArgs& a, hipStream_t stream) {
-    const dim3 block(kWave);
+hipError_t launch_retrieve(const RetrieveArgs& a, hipStream_t stream) {
+    if (a.n_query == 0) return hipSuccess;
     if (a.n_seg == 0) {
-        hipLaunchKernelGGL(retrieve_kernel<KMAX>, dim3(a.n_query), block, 0, stream, a);
+        // one batch of loads per lane where 16 waves suffice for that: 3000 entries took 17 us in one wave, 8.8 us in twelve
+        hipLaunchKernelGGL(retrieve_kernel, dim3(a.n_query), waves_for(a.n_bank, kUnroll * kWave), 0, stream, a);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(retrieve_segment_kernel<KMAX>, dim3((unsigned)a.n_query * a.n_seg), dim3(kSegWaves * kWave), 0,
+    hipLaunchKernelGGL(retrieve_segment_kernel, dim3(xcd_grid((unsigned)a.n_query * a.n_seg)), dim3(kSegWaves * kWave), 0,
                        stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(retrieve_merge_kernel<KMAX>, dim3(a.n_query), dim3(kMergeThreads), 0, stream, a);
+    hipLaunchKernelGGL(retrieve_merge_kernel, dim3(a.n_query), waves_for((int64_t)a.n_seg * a.k, kWave), 0, stream, a);
     return hipGetLastError();
-}
-
-hipError_t launch_retrieve(const RetrieveArgs& a, hipStream_t stream) {
-    if (a.n_query == 0) return hipSuccess;
-    if (a.k <= 4) return launch_k<4>(a, stream);
-    if (a.k <= 8) return launch_k<8>(a, stream);
-    if (a.k <= 16) return launch_k<16>(a, stream);
-    return launch_k<32>(a, stream);
 }
 
 }  // namespace revisit
