@@ -97,8 +97,8 @@ struct BiasGeom {
 // about half a tile's MFMAs (2 us) to land, in 64 registers. The queries, the
 // same for all waves, are read from LDS.
 //
-// Measured at H 12, D 128, Lq 4680, Lk 28080 (8.07e11 flops) with bias: 6.65 ms,
-// 121 TFLOP/s of the 154 that a large fp32 matrix product reaches here. The
+// Measured at H 12, D 128, Lq 4680, Lk 28080 (8.07e11 flops) with bias: 6.27 ms,
+// 129 TFLOP/s of the 154 that a large fp32 matrix product reaches here. The
 // kernel before it (128 queries per workgroup, tiles staged through registers
 // into LDS between two barriers, one 4-byte LDS read per MFMA) took 24.5 ms.
 // Four waves per item, two workgroups per compute unit: 7.48 ms. Lq 64, Lk 256,
@@ -108,8 +108,8 @@ constexpr int kF32Waves = 8;
 
 // The correspondence of a lane's query in KV frame f.
 struct F32Corr {
-    int f;      // -1: none loaded yet
-    int valid;  // retrieved frame, accepted correspondence
+    int f;       // -1: none loaded yet
+    float ng;    // -gamma, or 0 where the frame or the correspondence is not retrieved or accepted
     float ux, uy;
 };
 
@@ -126,32 +126,42 @@ __device__ __forceinline__ void f32_bias(floatx16& acc, F32Corr& c, const Attent
     for (;;) {
         if (f != c.f) {
             c.f = f;
-            c.valid = 0;
+            c.ng = c.ux = c.uy = 0.0f;
             const int s = __builtin_amdgcn_readfirstlane(a.slot[f]);
             if (s >= 0 && s < a.S && q_ok) {
                 const size_t o = (size_t)s * a.Lq + q;
                 const float2 u = reinterpret_cast<const float2*>(a.corr_uv)[o];
-                c.valid = a.corr_idx[o] >= 0;
-                c.ux = u.x;
-                c.uy = u.y;
+                if (a.corr_idx[o] >= 0) {
+                    c.ng = -g.gamma;
+                    c.ux = u.x;
+                    c.uy = u.y;
+                }
             }
+            // the loads are waited for here, once per frame: at the first use below
+            // the wait would also drain the key loads in flight, on every tile (that
+            // and a branch per logit: 6.65 ms at the size above instead of 6.27)
+            asm volatile("" : "+v"(c.ng), "+v"(c.ux), "+v"(c.uy));
         }
-        auto add = [&](auto row_of) __attribute__((always_inline)) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int t = t0 + acc_row(hh, i);
-                const int ky = row_of(t);
-                const int kx = t - ky * g.w;
-                const float dx = ((float)kx + 0.5f) - c.ux;
+        if (__any(c.ng != 0.0f)) {
+            auto value = [&](int t, int ky) -> float {
+                const float dx = ((float)(t - ky * g.w) + 0.5f) - c.ux;
                 const float dy = ((float)ky + 0.5f) - c.uy;
-                if (c.valid && t >= 0 && t < g.hw) acc[i] = -g.gamma * (dx * dx + dy * dy);
-            }
-        };
-        if (__any(c.valid)) {
+                return c.ng * (dx * dx + dy * dy);
+            };
             // (t + 1/2) / w truncates to t / w exactly below 2^20 keys per frame: its error is
             // under t 2^-22 / w, its distance from a whole number at least 1 / (2 w)
-            if (g.hw <= (1 << 20)) add([&](int t) { return (int)(((float)t + 0.5f) * inv_w); });
-            else add([&](int t) { return t / g.w; });
+            auto row = [&](int t) { return (int)(((float)t + 0.5f) * inv_w); };
+            if (t0 >= 0 && t0 + 32 <= g.hw && g.hw <= (1 << 20)) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[i] = value(t0 + acc_row(hh, i), row(t0 + acc_row(hh, i)));
+            } else {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int t = t0 + acc_row(hh, i);
+                    const float b = value(t, g.hw <= (1 << 20) ? row(t) : t / g.w);
+                    acc[i] = t >= 0 && t < g.hw ? b : acc[i];
+                }
+            }
         }
         if (t0 + span <= g.hw) break;  // the frame holds the tile's last key
         ++f;
@@ -216,7 +226,7 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_f32_kernel(AttentionArgs 
     for (int db = 0; db < kDb; ++db) O[db] = floatx16{0};
     float m_run = -INFINITY, l_run = 0.0f;
 
-    F32Corr corr{-1, 0, 0.0f, 0.0f};
+    F32Corr corr{-1, 0.0f, 0.0f, 0.0f};
 
     // one key tile (its keys are in kf) and the load of the wave's next one's keys
     auto tile = [&](auto full_tag, int k0, int k_next) __attribute__((always_inline)) {
