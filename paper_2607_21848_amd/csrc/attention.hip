@@ -933,7 +933,7 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttentionArgs a, Bias
     auto step_core = [&](auto kind_tag, int j, floatx16& S_cur, floatx16& S_next, const uint8_t* knext,
                          const uint32_t refill) __attribute__((always_inline)) {
         // kind 4: a step of the steady loop (kind 0 whose tiles j + 1 .. j + 3
-        // all lie inside Lk and are not the range's last)
+        // all lie inside Lk)
         constexpr bool kSteady = decltype(kind_tag)::value == 4;
         constexpr int kind = kSteady ? 0 : decltype(kind_tag)::value;
         constexpr bool has_next = kind != 3;
@@ -1175,9 +1175,11 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttentionArgs a, Bias
     mx_cur = t0 + 1 == n_tiles ? tile_max(True{}, Sa, tile0) : tile_max(False{}, Sa, tile0);
 
     // steady state in periods of six tiles, while each of them has at least
-    // three more after it
+    // three more after it. Its last step loads K tile j + 8 without the check
+    // against Lk, so where the part's last tile runs past Lk that one must not be it.
+    const int j_end = nt - 9 - ((t0 + nt) * kTK > Lk ? 1 : 0);
     int j = 0;
-    for (; j + 9 <= nt; j += 6) {
+    for (; j <= j_end; j += 6) {
         step(I0{}, I4{}, j);
         step(I1{}, I4{}, j + 1);
         step(I2{}, I4{}, j + 2);
@@ -1185,7 +1187,7 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttentionArgs a, Bias
         step(I4{}, I4{}, j + 4);
         step(I5{}, I4{}, j + 5);
     }
-    // the last 1 .. 8 tiles: one copy of the step body per kind, ring slot
+    // the last 1 .. 9 tiles: one copy of the step body per kind, ring slot
     // chosen at run time. The steady loop leaves off at a multiple of six, so
     // step j refills slot 0 and the logits of tile j are in Sa; after each
     // step the logits of tile j + 1 move from Sb to Sa.
