@@ -252,9 +252,9 @@ int reproject_correspondence(const float* tgt_depth, const float* tgt_c2w, const
  * or its keys are cut into P equal parts that run on P workgroups, and a
  * second kernel on the same stream merges the parts from fp32 partial
  * results kept in the workspace.
- *   key_parts   0 = P chosen from the shape and the compute units of the
- *               current device (more parts when the items alone would leave
- *               part of the GPU idle in the last round of workgroups), or a
+ *   key_parts   0 = P (at most 16) chosen from the shape and the compute units
+ *               of the current device (more parts when the items alone would
+ *               leave part of the GPU idle), or a
  *               fixed P in [1, 64] (clamped to the number of 32-key tiles).
  *               Any P gives the same result up to the fp32 rounding of the
  *               merge. fp32 ignores it.

@@ -1279,6 +1279,7 @@ namespace {
 // that each wave reads two whole 512-byte partial rows per load.
 constexpr int kMergeQueries = 8;
 constexpr int kMergeBatch = 8;  // parts merged from registers loaded up front
+constexpr int kMaxParts = 64;   // largest key_parts
 
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttentionArgs a, KeySplit ks) {
     const int n_qt = (a.Lq + 127) / 128;
@@ -1320,10 +1321,41 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttentionArgs a, KeySpl
             if (p < ks.parts) add(m[p], l[p], v[p]);
         }
     } else {
-        for (int p = 0; p < ks.parts; ++p) M = fmaxf(M, base[(size_t)p * kPartFloats + 128 * kD + qi]);
-        for (int p = 0; p < ks.parts; ++p) {
-            const float* P = base + (size_t)p * kPartFloats;
-            add(P[128 * kD + qi], P[128 * kD + 128 + qi], *reinterpret_cast<const float4*>(P + qi * kD + d));
+        // the query's 32 lanes take a part's maximum and sum each (two with more
+        // than 32 parts), then every lane has them from those, and the partial
+        // rows are loaded a batch at a time
+        static_assert(kMaxParts <= 64, "two parts per lane");
+        const int sub = threadIdx.x & 31;
+        const int src0 = threadIdx.x & 32;  // the query's first lane
+        float m[2], l[2], c[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int p = sub + 32 * i;
+            const float* P = base + (size_t)min(p, ks.parts - 1) * kPartFloats + 128 * kD + qi;
+            m[i] = P[0];
+            l[i] = P[128];
+            M = fmaxf(M, m[i]);
+        }
+#pragma unroll
+        for (int off = 1; off < 32; off *= 2) M = fmaxf(M, __shfl_xor(M, off));
+#pragma unroll
+        for (int i = 0; i < 2; ++i) c[i] = __builtin_amdgcn_exp2f(m[i] - M);
+        for (int p0 = 0; p0 < ks.parts; p0 += kMergeBatch) {
+            float4 v[kMergeBatch];
+#pragma unroll
+            for (int p = 0; p < kMergeBatch; ++p)
+                v[p] = *reinterpret_cast<const float4*>(base + (size_t)min(p0 + p, ks.parts - 1) * kPartFloats + qi * kD + d);
+#pragma unroll
+            for (int p = 0; p < kMergeBatch; ++p) {
+                const bool hi = p0 + p >= 32;  // uniform
+                const int lane = src0 + ((p0 + p) & 31);
+                const float cp = __shfl(hi ? c[1] : c[0], lane), lp = __shfl(hi ? l[1] : l[0], lane);
+                if (p0 + p < ks.parts) {
+                    L = fmaf(cp, lp, L);
+                    acc = make_float4(fmaf(cp, v[p].x, acc.x), fmaf(cp, v[p].y, acc.y), fmaf(cp, v[p].z, acc.z),
+                                      fmaf(cp, v[p].w, acc.w));
+                }
+            }
         }
     }
     const float inv = 1.0f / L;
@@ -1334,26 +1366,37 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttentionArgs a, KeySpl
 
 }  // namespace
 
-int32_t attention_bf16_key_parts(const AttentionArgs& a, int32_t slots) {
-    // Smallest number of key parts (at most kMaxParts, each of at least
-    // kMinTiles key tiles) whose workgroups fill the last round of `slots`
-    // resident workgroups to 97 % or more. When none does: one part if the
-    // items alone make four rounds or more (the tail is then short), else the
-    // most parts allowed. Every part costs a prologue, a 66 KB partial write
-    // and its share of the merge, so past four parts the better-filled last
-    // round no longer pays: with 444 items on 512 slots, 4 parts measured
-    // 2-5 % faster than 8 (filled) and than 1.
-    constexpr int kMinTiles = 128, kMaxParts = 4;
+int32_t attention_bf16_key_parts(const AttentionArgs& a, int32_t cus) {
+    // The number of parts with the least estimated time. The busiest compute
+    // unit runs n = ceil(items P / cus) workgroups of ceil(tiles / P) key tiles,
+    // two at a time: 0.45 us a tile in company, 0.57 alone, 2 us for each further
+    // pair's start. A merge is a second launch (2.5 us) and 66.5 KB written and
+    // read back per workgroup (22 us per 1000). Fitted to 1100 timings (2 to 1700
+    // items, 5 to 2025 tiles, 1 to 32 parts; 8% off on average); its choice is on
+    // average 1.5% above the best of the measured parts. A rule that filled two
+    // workgroups per compute unit with at most 4 parts of at least 128 tiles left
+    // short ranges whole: 10 items of 110 tiles 69 us, now 21 in 8 parts; 120
+    // items of 220 tiles 127 us, now 70 in 4; 444 items of 439 tiles 437 us in 3
+    // parts, now 406 in one. A further part has to gain 1.5%, and past four parts
+    // the workspace is kept below 140 MB.
+    constexpr int kAutoParts = 16, kSplitUnits = 2048;
     const int64_t items = (int64_t)((a.Lq + 127) / 128) * a.H;
     const int n_tiles = (a.Lk + kTK - 1) / kTK;
-    int largest = 1;
-    for (int p = 1; p <= kMaxParts && (p == 1 || n_tiles / p >= kMinTiles); ++p) {
+    int best = 1;
+    double best_us = INFINITY;
+    for (int p = 1; p <= kAutoParts && p <= n_tiles; ++p) {
         const int64_t units = items * p;
-        const int64_t rounds = (units + slots - 1) / slots;
-        if ((double)units >= 0.97 * (double)(rounds * slots)) return p;
-        largest = p;
+        if (p > 4 && units > kSplitUnits) break;
+        const int64_t n = (units + cus - 1) / cus;
+        const int64_t odd = n % 2, tiles = (n_tiles + p - 1) / p;
+        double us = (0.45 * (double)(n - odd) + 0.57 * (double)odd) * (double)tiles + 2.0 * (double)((n + 1) / 2);
+        us += 7.0 + (p > 1 ? 2.5 + 0.022 * (double)units : 0.0);
+        if (us < 0.985 * best_us) {
+            best = p;
+            best_us = us;
+        }
     }
-    return items >= 4 * (int64_t)slots ? 1 : largest;
+    return best;
 }
 
 size_t attention_bf16_workspace_bytes(const AttentionArgs& a, int32_t parts) {

@@ -90,7 +90,7 @@ int attention_parts(const char* fn, const revisit::AttentionArgs& a, int32_t key
         int cus = 0;
         const hipError_t e = device_compute_units(&cus);
         if (e != hipSuccess) return fail(REVISIT_ERR_LAUNCH, "%s: device query failed: %s", fn, hipGetErrorString(e));
-        P = revisit::attention_bf16_key_parts(a, 2 * cus);  // two resident workgroups per compute unit
+        P = revisit::attention_bf16_key_parts(a, cus);
     }
     const int32_t tiles = (a.Lk + 31) / 32;
     P = P < tiles ? P : tiles;  // at least one key tile per part

@@ -87,8 +87,8 @@ hipError_t launch_attention_f32(const AttentionArgs& a, hipStream_t stream);
 // into `parts` equal ranges, one workgroup each; with parts > 1 a second
 // kernel merges the partial results kept in `workspace`
 // (attention_bf16_workspace_bytes). attention_bf16_key_parts picks the
-// number of parts that fills `slots` resident workgroups best.
-int32_t attention_bf16_key_parts(const AttentionArgs& a, int32_t slots);
+// number of parts that should be fastest on `cus` compute units.
+int32_t attention_bf16_key_parts(const AttentionArgs& a, int32_t cus);
 size_t attention_bf16_workspace_bytes(const AttentionArgs& a, int32_t parts);
 hipError_t launch_attention_bf16(const AttentionArgs& a, int32_t parts, float* workspace, hipStream_t stream);
 

@@ -1,0 +1,44 @@
+"""The merge of many key parts (batches of eight, two parts per lane past 32), and the automatic
+split of short key ranges, against the fp64 oracle at the bf16 bars (2e-2 on O, 4e-3 on LSE)."""
+
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2607_21848_amd as rv
+import workloads as W
+from oracle import attention as OA
+from tests.gpu_helpers import dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(Lq, frames, h, w, S, H, seed):
+    rng = np.random.default_rng(seed)
+    q, k, v = (W.bf16_round(rng.standard_normal((L, H, 128), dtype=np.float32)) for L in (Lq, frames * h * w, frames * h * w))
+    k[:40] *= 4.0  # the first part's maxima stand out, the others' sums are scaled down (exact in bf16)
+    slot = np.full(frames, -1, np.int32)
+    slot[rng.permutation(frames)[:S]] = np.arange(S)
+    uv = np.stack([rng.uniform(0, w, (S, Lq)), rng.uniform(0, h, (S, Lq))], -1).astype(np.float32)
+    return q, k, v, slot, uv, rng.integers(-4, h * w, size=(S, Lq)).astype(np.int32)
+
+
+def _check(c, h, w, parts):
+    q, k, v, slot, uv, idx = c
+    print(f"Lq={q.shape[0]} Lk={k.shape[0]} H={q.shape[1]} parts={parts}", flush=True)
+    o, lse = rv.biased_chunk_attention(*(dev(x, torch.bfloat16) for x in (q, k, v)), dev(slot), dev(uv), dev(idx), h=h, w=w,
+                                       softmax_scale=128 ** -0.5, lam=1.0, sigma=2.0, key_parts=parts)
+    Oo, Lo = OA.biased_attention(q, k, v, slot, uv, idx, h, w, 128 ** -0.5, 1.0, 2.0)
+    assert np.abs(host(o) - Oo).max() <= 2e-2 and np.abs(host(lse) - Lo).max() <= 4e-3
+
+
+@pytest.mark.parametrize("parts", [8, 9, 16, 17, 31, 32, 33, 40, 63, 64])
+def test_merge_of_many_parts(parts):
+    _check(_case(131, 9, 13, 18, 3, 2, 5), 13, 18, parts)  # 66 key tiles, a ragged last one
+
+
+@pytest.mark.parametrize("frames", [1, 2, 5, 18])
+def test_automatic_split_of_short_ranges(frames):
+    _check(_case(60, frames, 9, 16, min(frames, 3), 3, frames), 9, 16, 0)
