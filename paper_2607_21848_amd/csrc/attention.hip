@@ -186,20 +186,23 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_f32_kernel(AttentionArgs 
     const int n = lane & 31;
     // items head-major, each XCD a contiguous range: one head's keys and values meet in one L2
     const int n_qt = (a.Lq + 31) / 32;
-    const unsigned n_items = (unsigned)n_qt * (unsigned)a.H;
+    const unsigned n_items = (unsigned)n_qt * (unsigned)(a.H * a.layers);
     const unsigned item = xcd_item(blockIdx.x, n_items);
     if (item >= n_items) return;  // grid padding (uniform, before any barrier)
-    const int hd = (int)(item / (unsigned)n_qt);
-    const int q = (int)(item - (unsigned)hd * (unsigned)n_qt) * 32 + n;
+    const int lh = (int)(item / (unsigned)n_qt);  // layer and head
+    const int layer = lh / a.H;
+    const int hd = lh - layer * a.H;
+    const int q = (int)(item - (unsigned)lh * (unsigned)n_qt) * 32 + n;
     const bool q_ok = q < a.Lq;
     const int Lk = a.Lk;
     const int n_tiles = (Lk + TK - 1) / TK;
     const uint32_t row_bytes = (uint32_t)a.H * D * 4;  // at most 2^25
-    const uint8_t* Kg = static_cast<const uint8_t*>(a.k) + (size_t)hd * D * 4;
-    const uint8_t* Vg = static_cast<const uint8_t*>(a.v) + (size_t)hd * D * 4;
+    const size_t q_row0 = (size_t)layer * a.q_rows, kv_byte0 = (size_t)layer * a.kv_rows * row_bytes + (size_t)hd * D * 4;
+    const uint8_t* Kg = static_cast<const uint8_t*>(a.k) + kv_byte0;
+    const uint8_t* Vg = static_cast<const uint8_t*>(a.v) + kv_byte0;
 
     for (int j = wave; j < kG; j += kF32Waves) {
-        const float* Qg = static_cast<const float*>(a.q) + ((size_t)q * a.H + hd) * D + 4 * hh;
+        const float* Qg = static_cast<const float*>(a.q) + ((q_row0 + q) * a.H + hd) * D + 4 * hh;
         lds_q[j][lane] = q_ok ? *reinterpret_cast<const floatx4*>(Qg + 8 * j) : floatx4{0, 0, 0, 0};
     }
 
@@ -342,7 +345,7 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_f32_kernel(AttentionArgs 
     }
     if (wave == 0 && q_ok) {
         const float inv = 1.0f / l_tot;
-        float* Og = static_cast<float*>(a.o) + ((size_t)q * a.H + hd) * D;
+        float* Og = static_cast<float*>(a.o) + ((q_row0 + q) * a.H + hd) * D;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             vvec o;
@@ -350,7 +353,7 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_f32_kernel(AttentionArgs 
             for (int db = 0; db < kDb; ++db) o[db] = O[db][i] * inv;
             *reinterpret_cast<vvec*>(Og + kDb * acc_row(hh, i)) = o;
         }
-        if (a.lse && hh == 0) a.lse[(size_t)hd * a.Lq + q] = (M + log2f(l_tot)) * kLn2;
+        if (a.lse && hh == 0) a.lse[(size_t)lh * a.Lq + q] = (M + log2f(l_tot)) * kLn2;
     }
 }
 
@@ -615,23 +618,25 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttentionArgs a, Bias
     const int n_qt = (a.Lq + 127) / 128;
     const int Lk = a.Lk;
     const int n_tiles = (Lk + kTK - 1) / kTK;
-    const unsigned n_units = (unsigned)(n_qt * a.H * ks.parts);
+    const unsigned n_units = (unsigned)(n_qt * a.H * a.layers * ks.parts);
     const unsigned unit = xcd_item(blockIdx.x, n_units);
     if (unit >= n_units) return;  // grid padding (uniform, before any barrier)
     const int qt = (int)(unit % (unsigned)n_qt);
     const int hp = (int)(unit / (unsigned)n_qt);
-    const int hd = hp / ks.parts;
-    const int kp = hp - hd * ks.parts;
+    const int lh = hp / ks.parts;  // layer and head
+    const int kp = hp - lh * ks.parts;
+    const int layer = lh / a.H;
+    const int hd = lh - layer * a.H;
     const int t0 = (int)((int64_t)kp * n_tiles / ks.parts);
     const int nt = (int)((int64_t)(kp + 1) * n_tiles / ks.parts) - t0;
     const int H = a.H;
     using KFmt = std::conditional_t<kFp8, RowsFp8, RowsBf16>;
-    const uint8_t* Qg = static_cast<const uint8_t*>(a.q);
-    const uint8_t* Kg = static_cast<const uint8_t*>(a.k);
-    const uint8_t* Vg = static_cast<const uint8_t*>(a.v);
     const size_t row_stride = (size_t)H * kD;              // elements between consecutive tokens (o)
     const size_t qk_row_bytes = row_stride * (kFp8 ? 1 : 2);
     const size_t v_row_bytes = row_stride * 2;
+    const uint8_t* Qg = static_cast<const uint8_t*>(a.q) + (size_t)layer * a.q_rows * qk_row_bytes;
+    const uint8_t* Kg = static_cast<const uint8_t*>(a.k) + (size_t)layer * a.kv_rows * qk_row_bytes;
+    const uint8_t* Vg = static_cast<const uint8_t*>(a.v) + (size_t)layer * a.kv_rows * v_row_bytes;
     using R0 = std::integral_constant<int, 0>;
     using R1 = std::integral_constant<int, 1>;
     using R2 = std::integral_constant<int, 2>;
@@ -1210,7 +1215,7 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttentionArgs a, Bias
         // the whole key range: normalise and store
         const float inv = 1.0f / l_tot;
         if (q_ok) {
-            uint16_t* Og = static_cast<uint16_t*>(a.o) + (size_t)q * row_stride + (size_t)hd * kD;
+            uint16_t* Og = static_cast<uint16_t*>(a.o) + ((size_t)layer * a.q_rows + q) * row_stride + (size_t)hd * kD;
 #pragma unroll
             for (int db = 0; db < 4; ++db) {
 #pragma unroll
@@ -1221,12 +1226,12 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttentionArgs a, Bias
                     *reinterpret_cast<uint2*>(Og + d) = make_uint2(w0, w1);
                 }
             }
-            if (a.lse && hh == 0) a.lse[(size_t)hd * a.Lq + q] = (m_run + log2f(l_tot)) * kLn2;
+            if (a.lse && hh == 0) a.lse[(size_t)lh * a.Lq + q] = (m_run + log2f(l_tot)) * kLn2;
         }
     } else {
         // one part of the key range: unnormalised O with its running max and
         // sum, merged by attn_merge_kernel
-        float* part = ks.part + ((size_t)(hd * n_qt + qt) * ks.parts + kp) * kPartFloats;
+        float* part = ks.part + (((size_t)lh * n_qt + qt) * ks.parts + kp) * kPartFloats;
         const int qi = wave * 32 + n;
 #pragma unroll
         for (int db = 0; db < 4; ++db) {
@@ -1261,7 +1266,7 @@ hipError_t launch_attention_f32(const AttentionArgs& a, hipStream_t stream) {
     if (a.Lq == 0) return hipSuccess;
     const BiasGeom g = make_geom(a);
     const bool bias_on = a.S > 0 && a.lambda != 0.0f;
-    const dim3 grid(xcd_grid((unsigned)((a.Lq + 31) / 32) * (unsigned)a.H)), block(64 * kF32Waves);
+    const dim3 grid(xcd_grid((unsigned)((a.Lq + 31) / 32) * (unsigned)(a.H * a.layers))), block(64 * kF32Waves);
     const float c = a.softmax_scale * kLog2e;
     if (a.D == 64) {
         hipLaunchKernelGGL(attn_f32_kernel<64>, grid, block, 0, stream, a, g, c, bias_on);
@@ -1286,8 +1291,9 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttentionArgs a, KeySpl
     const int item = blockIdx.x / (128 / kMergeQueries);
     const int qi = (blockIdx.x % (128 / kMergeQueries)) * kMergeQueries + (threadIdx.x >> 5);
     const int d = 4 * (threadIdx.x & 31);
-    const int hd = item / n_qt;
-    const int q = (item - hd * n_qt) * 128 + qi;
+    const int lh = item / n_qt;  // layer and head
+    const int layer = lh / a.H;
+    const int q = (item - lh * n_qt) * 128 + qi;
     if (q >= a.Lq) return;
     const float* base = ks.part + (size_t)item * ks.parts * kPartFloats;
     float M = -INFINITY;
@@ -1359,9 +1365,9 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttentionArgs a, KeySpl
         }
     }
     const float inv = 1.0f / L;
-    uint16_t* Og = static_cast<uint16_t*>(a.o) + (size_t)q * a.H * kD + (size_t)hd * kD + d;
+    uint16_t* Og = static_cast<uint16_t*>(a.o) + (((size_t)layer * a.q_rows + q) * a.H + (lh - layer * a.H)) * kD + d;
     *reinterpret_cast<uint2*>(Og) = make_uint2(cvt_pk_bf16(acc.x * inv, acc.y * inv), cvt_pk_bf16(acc.z * inv, acc.w * inv));
-    if (a.lse && d == 0) a.lse[(size_t)hd * a.Lq + q] = (M + log2f(L)) * kLn2;
+    if (a.lse && d == 0) a.lse[(size_t)lh * a.Lq + q] = (M + log2f(L)) * kLn2;
 }
 
 }  // namespace
@@ -1378,15 +1384,16 @@ int32_t attention_bf16_key_parts(const AttentionArgs& a, int32_t cus) {
     // short ranges whole: 10 items of 110 tiles 69 us, now 21 in 8 parts; 120
     // items of 220 tiles 127 us, now 70 in 4; 444 items of 439 tiles 437 us in 3
     // parts, now 406 in one. A further part has to gain 1.5%, and past four parts
-    // the workspace is kept below 140 MB.
+    // (past one where a launch takes several layers) the workspace is kept below
+    // 140 MB.
     constexpr int kAutoParts = 16, kSplitUnits = 2048;
-    const int64_t items = (int64_t)((a.Lq + 127) / 128) * a.H;
+    const int64_t items = (int64_t)((a.Lq + 127) / 128) * a.H * a.layers;
     const int n_tiles = (a.Lk + kTK - 1) / kTK;
     int best = 1;
     double best_us = INFINITY;
     for (int p = 1; p <= kAutoParts && p <= n_tiles; ++p) {
         const int64_t units = items * p;
-        if (p > 4 && units > kSplitUnits) break;
+        if ((p > 4 || (p > 1 && a.layers > 1)) && units > kSplitUnits) break;
         const int64_t n = (units + cus - 1) / cus;
         const int64_t odd = n % 2, tiles = (n_tiles + p - 1) / p;
         double us = (0.45 * (double)(n - odd) + 0.57 * (double)odd) * (double)tiles + 2.0 * (double)((n + 1) / 2);
@@ -1401,7 +1408,7 @@ int32_t attention_bf16_key_parts(const AttentionArgs& a, int32_t cus) {
 
 size_t attention_bf16_workspace_bytes(const AttentionArgs& a, int32_t parts) {
     if (parts <= 1) return 0;
-    const int64_t items = (int64_t)((a.Lq + 127) / 128) * a.H;
+    const int64_t items = (int64_t)((a.Lq + 127) / 128) * a.H * a.layers;
     return (size_t)items * parts * kPartFloats * sizeof(float);
 }
 
@@ -1441,7 +1448,7 @@ hipError_t launch_attention_bf16(const AttentionArgs& a, int32_t parts, float* w
     if (a.Lq == 0) return hipSuccess;
     const BiasGeom g = make_geom(a);
     const bool bias_on = a.S > 0 && a.lambda != 0.0f;
-    const unsigned items = (unsigned)(((a.Lq + 127) / 128) * a.H);
+    const unsigned items = (unsigned)(((a.Lq + 127) / 128) * a.H * a.layers);
     const KeySplit ks{parts, workspace};
     const dim3 grid(xcd_grid(items * (unsigned)parts)), block(256);
     const float c_log2 = a.softmax_scale * kLog2e;

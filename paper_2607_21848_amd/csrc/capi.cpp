@@ -82,7 +82,7 @@ int check_attention_shape(const char* fn, int32_t dtype, int32_t Lq, int32_t Lk,
 }
 
 // Key parts of the bf16 / fp8 kernel for this call (0 = automatic), and the
-// workspace bytes they need. AttentionArgs needs only Lq, Lk and H here.
+// workspace bytes they need. AttentionArgs needs only Lq, Lk, H and layers here.
 int attention_parts(const char* fn, const revisit::AttentionArgs& a, int32_t key_parts, int32_t* parts,
                     size_t* bytes) {
     int32_t P = key_parts;
@@ -334,10 +334,67 @@ int prepare_attention(const char* fn, const void* q, const void* k, const void* 
     a.lambda = lambda;
     a.sigma = sigma;
     a.fp8_qk = dtype == REVISIT_FP8_QK;
+    a.layers = 1;
+    a.q_rows = 0;
+    a.kv_rows = 0;
     return REVISIT_OK;
 }
 
+// The launch with the caller's workspace.
+int run_attention(const char* fn, const revisit::AttentionArgs& a, int32_t dtype, int32_t key_parts, void* workspace,
+                  size_t workspace_bytes, hipStream_t stream) {
+    if (dtype == REVISIT_F32) return launched(revisit::launch_attention_f32(a, stream), fn);
+    int32_t parts = 1;
+    size_t need = 0;
+    int st = attention_parts(fn, a, key_parts, &parts, &need);
+    if (st != REVISIT_OK) return st;
+    st = check_workspace(fn, need, workspace, workspace_bytes);
+    if (st != REVISIT_OK) return st;
+    return launched(revisit::launch_attention_bf16(a, parts, static_cast<float*>(workspace), stream), fn);
+}
+
 }  // namespace
+
+namespace revisit {
+
+int attention_layers(const char* fn, const void* q, const void* k, const void* v, void* o, float* lse, int32_t dtype,
+                     int32_t Lq, int32_t Lk, int32_t H, int32_t D, int32_t h, int32_t w, const int32_t* kv_frame_slot,
+                     const float* corr_uv, const int32_t* corr_idx, int32_t S, float softmax_scale, float lambda,
+                     float sigma, int32_t layers, int32_t q_rows, int32_t kv_rows, void* workspace,
+                     size_t workspace_bytes, hipStream_t stream) {
+    AttentionArgs a{};
+    bool nothing = false;
+    const int st = prepare_attention(fn, q, k, v, o, lse, dtype, Lq, Lk, H, D, h, w, kv_frame_slot, corr_uv, corr_idx, S,
+                                     softmax_scale, lambda, sigma, 0, a, &nothing);
+    if (st != REVISIT_OK || nothing) return st;
+    a.layers = layers;
+    a.q_rows = q_rows;
+    a.kv_rows = kv_rows;
+    return run_attention(fn, a, dtype, 0, workspace, workspace_bytes, stream);
+}
+
+int attention_layers_workspace(const char* fn, int32_t dtype, int32_t Lq, int32_t Lk, int32_t H, int32_t D,
+                               int32_t layers, size_t* bytes) {
+    *bytes = 0;
+    const int st = check_attention_shape(fn, dtype, Lq, Lk, H, D, 0);
+    if (st != REVISIT_OK || dtype == REVISIT_F32 || Lq == 0) return st;
+    AttentionArgs a{};
+    a.Lq = Lq;
+    a.Lk = Lk;
+    a.H = H;
+    a.layers = layers;
+    int32_t parts = 1;
+    return attention_parts(fn, a, 0, &parts, bytes);
+}
+
+int32_t attention_max_layers(int32_t Lq, int32_t H, int32_t layers) {
+    // 32-query items (fp32) or 128-query items in at most 16 parts (bf16)
+    const int64_t per_layer = (((int64_t)Lq + 31) / 32 + 16 * (((int64_t)Lq + 127) / 128)) * H;
+    const int64_t most = ((int64_t)1 << 30) / (per_layer > 0 ? per_layer : 1);
+    return most < 1 ? 1 : (int32_t)(most < layers ? most : layers);
+}
+
+}  // namespace revisit
 
 extern "C" {
 
@@ -351,15 +408,7 @@ int biased_chunk_attention(const void* q, const void* k, const void* v, void* o,
     int st = prepare_attention("biased_chunk_attention", q, k, v, o, lse, dtype, Lq, Lk, H, D, h, w, kv_frame_slot,
                                corr_uv, corr_idx, S, softmax_scale, lambda, sigma, key_parts, a, &nothing);
     if (st != REVISIT_OK || nothing) return st;
-    if (dtype == REVISIT_F32) return launched(revisit::launch_attention_f32(a, stream), "biased_chunk_attention");
-    int32_t parts = 1;
-    size_t need = 0;
-    st = attention_parts("biased_chunk_attention", a, key_parts, &parts, &need);
-    if (st != REVISIT_OK) return st;
-    st = check_workspace("biased_chunk_attention", need, workspace, workspace_bytes);
-    if (st != REVISIT_OK) return st;
-    return launched(revisit::launch_attention_bf16(a, parts, static_cast<float*>(workspace), stream),
-                    "biased_chunk_attention");
+    return run_attention("biased_chunk_attention", a, dtype, key_parts, workspace, workspace_bytes, stream);
 }
 
 int biased_chunk_attention_noalloc(const void* q, const void* k, const void* v, void* o, float* lse, int32_t dtype,
@@ -407,6 +456,7 @@ int rc_attention_workspace_size(int32_t dtype, int32_t Lq, int32_t Lk, int32_t H
     a.Lq = Lq;
     a.Lk = Lk;
     a.H = H;
+    a.layers = 1;
     int32_t parts = 1;
     return attention_parts("rc_attention_workspace_size", a, key_parts, &parts, bytes);
 }

@@ -80,6 +80,11 @@ struct AttentionArgs {
     int32_t S;  // 0 = bias off
     float softmax_scale, lambda, sigma;
     int32_t fp8_qk;  // bf16 kernel: q and k are fp8 e4m3 (v, o bf16)
+    // `layers` problems of this shape in one launch, sharing slots and
+    // correspondences: layer l's q and o start l q_rows token rows further, its
+    // k and v l kv_rows, its lse l H Lq values
+    int32_t layers;
+    int32_t q_rows, kv_rows;
 };
 hipError_t launch_attention_f32(const AttentionArgs& a, hipStream_t stream);
 
@@ -91,6 +96,19 @@ hipError_t launch_attention_f32(const AttentionArgs& a, hipStream_t stream);
 int32_t attention_bf16_key_parts(const AttentionArgs& a, int32_t cus);
 size_t attention_bf16_workspace_bytes(const AttentionArgs& a, int32_t parts);
 hipError_t launch_attention_bf16(const AttentionArgs& a, int32_t parts, float* workspace, hipStream_t stream);
+
+// biased_chunk_attention over `layers` layers in one launch (capi.cpp): the
+// same arguments for layer 0 plus the row strides of AttentionArgs, and the
+// workspace bytes it needs.
+int attention_layers(const char* fn, const void* q, const void* k, const void* v, void* o, float* lse, int32_t dtype,
+                     int32_t Lq, int32_t Lk, int32_t H, int32_t D, int32_t h, int32_t w, const int32_t* kv_frame_slot,
+                     const float* corr_uv, const int32_t* corr_idx, int32_t S, float softmax_scale, float lambda,
+                     float sigma, int32_t layers, int32_t q_rows, int32_t kv_rows, void* workspace,
+                     size_t workspace_bytes, hipStream_t stream);
+int attention_layers_workspace(const char* fn, int32_t dtype, int32_t Lq, int32_t Lk, int32_t H, int32_t D,
+                               int32_t layers, size_t* bytes);
+// Layers that one launch takes at most (a 32-bit count of workgroups).
+int32_t attention_max_layers(int32_t Lq, int32_t H, int32_t layers);
 
 // Scratch of biased_chunk_attention_noalloc: a file-scope device array in
 // attention.hip of kAttentionScratchBytes, one per device for the life of the

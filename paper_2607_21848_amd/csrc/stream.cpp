@@ -164,14 +164,18 @@ int rc_stream_create(const rc_stream_config* cfg, rc_stream** out) {
     // workspace of the largest step on this device: attention over 1..5 parts of
     // T keys (the automatic key split), retrieval over up to max_chunks entries
     size_t ws = 0;
+    const int32_t at_once = revisit::attention_max_layers((int32_t)T, c.H, c.layers);
     for (int32_t np = 1; np <= revisit::kStreamMaxParts; ++np) {
-        size_t b = 0;
-        const int st = rc_attention_workspace_size(c.dtype, (int32_t)T, np * (int32_t)T, c.H, c.D, 0, &b);
-        if (st != REVISIT_OK) {
-            delete s;
-            return st;
+        for (int32_t l0 = 0; l0 < c.layers; l0 += at_once) {
+            size_t b = 0;
+            const int st = revisit::attention_layers_workspace("rc_stream_create", c.dtype, (int32_t)T, np * (int32_t)T, c.H,
+                                                               c.D, at_once < c.layers - l0 ? at_once : c.layers - l0, &b);
+            if (st != REVISIT_OK) {
+                delete s;
+                return st;
+            }
+            ws = b > ws ? b : ws;
         }
-        ws = b > ws ? b : ws;
     }
     {
         size_t b = 0;
@@ -315,15 +319,18 @@ int rc_stream_step(rc_stream* s, const float* depth, const float* c2w, const flo
         i0 = i1;
     }
 
-    // biased attention of every layer over its packed cache
+    // biased attention of every layer over its packed cache, all layers in one launch: one layer
+    // alone leaves the last round of workgroups part empty and needs its keys split and merged
     const int32_t Lk = n_parts * T;
-    for (int32_t l = 0; l < c.layers; ++l) {
+    const int32_t at_once = revisit::attention_max_layers(T, c.H, c.layers);
+    for (int32_t l = 0; l < c.layers; l += at_once) {
         const size_t qo = (size_t)l * T * row, co = (size_t)l * s->max_rows * row;
-        st = biased_chunk_attention(static_cast<const uint8_t*>(q) + qo, static_cast<const uint8_t*>(s->cache_k) + co,
-                                    static_cast<const uint8_t*>(s->cache_v) + co, static_cast<uint8_t*>(o) + qo,
-                                    lse ? lse + (size_t)l * c.H * T : nullptr, c.dtype, T, Lk, c.H, c.D, c.h, c.w,
-                                    s->kv_slot, s->corr_uv, s->corr_idx, ret_part >= 0 ? F : 0, c.softmax_scale,
-                                    c.lambda, c.sigma, 0, s->workspace, s->workspace_bytes, stream);
+        st = revisit::attention_layers("rc_stream_step", static_cast<const uint8_t*>(q) + qo,
+                                       static_cast<const uint8_t*>(s->cache_k) + co, static_cast<const uint8_t*>(s->cache_v) + co,
+                                       static_cast<uint8_t*>(o) + qo, lse ? lse + (size_t)l * c.H * T : nullptr, c.dtype, T, Lk,
+                                       c.H, c.D, c.h, c.w, s->kv_slot, s->corr_uv, s->corr_idx, ret_part >= 0 ? F : 0,
+                                       c.softmax_scale, c.lambda, c.sigma, at_once < c.layers - l ? at_once : c.layers - l, T,
+                                       s->max_rows, s->workspace, s->workspace_bytes, stream);
         if (st != REVISIT_OK) return st;
     }
     s->last_n = n;
