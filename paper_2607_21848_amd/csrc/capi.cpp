@@ -102,6 +102,62 @@ int attention_parts(const char* fn, const revisit::AttentionArgs& a, int32_t key
 }  // namespace
 
 namespace revisit {
+
+int retrieve_with_slots(const char* fn, const float* bank_c2w, int32_t n_bank, const float* query_c2w,
+                        const int32_t* query_chunk, int32_t n_query, float E, float w_v, float tau_c, float tau_v,
+                        int32_t delta, int32_t first_candidate, int32_t k, int32_t* out_idx, float* out_score,
+                        int32_t* out_count, int32_t frames_per_chunk, int32_t* out_frame_sel, const StreamSlotsArgs* slots,
+                        void* workspace, size_t workspace_bytes, hipStream_t stream) {
+    size_t need = 0;
+    int st = rc_retrieve_workspace_size(n_bank, n_query, k, &need);
+    if (st != REVISIT_OK) return st;
+    if (!(finite(E) && E > 0.0f)) return fail(REVISIT_ERR_PARAM, "%s: E must be finite and > 0", fn);
+    if (!finite(w_v) || !finite(tau_c) || !finite(tau_v))
+        return fail(REVISIT_ERR_PARAM, "%s: w_v, tau_c and tau_v must be finite", fn);
+    if (out_frame_sel && (frames_per_chunk < 1 || (int64_t)k * frames_per_chunk > (1 << 20)))
+        return fail(REVISIT_ERR_PARAM, "%s: frames_per_chunk=%d invalid", fn, frames_per_chunk);
+    if (n_query == 0) return REVISIT_OK;
+    if (!query_c2w || !query_chunk || !out_idx || !out_count || (n_bank > 0 && !bank_c2w))
+        return fail(REVISIT_ERR_NULL, "%s: required pointer is NULL", fn);
+    // the scan reads the pose columns it needs as 8-byte pairs
+    if (!aligned(bank_c2w, 8)) return fail(REVISIT_ERR_SHAPE, "%s: bank_c2w must be 8-byte aligned", fn);
+    RetrieveArgs a{};
+    a.bank_c2w = bank_c2w;
+    a.n_bank = n_bank;
+    a.query_c2w = query_c2w;
+    a.query_chunk = query_chunk;
+    a.n_query = n_query;
+    a.E = (double)E;
+    a.w_v = (double)w_v;
+    a.tau_c = (double)tau_c;
+    a.cos_tau_v = cos((double)tau_v);
+    // above (tau_c E)^2 (1 + 1e-9) the definition's sqrt(x) / E exceeds tau_c: its two roundings move it by
+    // 2^-52 of its value. fp32 tau_c and E keep the square between 1e-180 and 1e154 unless it is 0.
+    a.reach2 = (a.tau_c * a.E) * (a.tau_c * a.E) * (1.0 + 1e-9);
+    a.delta = delta;
+    a.first_candidate = first_candidate;
+    a.k = k;
+    a.out_idx = out_idx;
+    a.out_score = out_score;
+    a.out_count = out_count;
+    a.frames_per_chunk = frames_per_chunk;
+    a.out_frame_sel = out_frame_sel;
+    a.n_seg = revisit::retrieve_segments(n_bank);
+    a.seg_s = nullptr;
+    a.seg_j = nullptr;
+    if (slots) {
+        a.with_slots = 1;
+        a.slots = *slots;
+    }
+    st = check_workspace(fn, need, workspace, workspace_bytes);
+    if (st != REVISIT_OK) return st;
+    if (a.n_seg > 0) {
+        a.seg_s = static_cast<double*>(workspace);
+        a.seg_j = reinterpret_cast<int32_t*>(a.seg_s + (size_t)a.n_seg * n_query * k);
+    }
+    return launched(launch_retrieve(a, stream), fn);
+}
+
 int fail_status(int status, const char* fmt, ...) {
     va_list ap;
     va_start(ap, fmt);
@@ -133,50 +189,9 @@ int retrieve_chunks(const float* bank_c2w, int32_t n_bank, const float* query_c2
                     int32_t first_candidate, int32_t k, int32_t* out_idx, float* out_score, int32_t* out_count,
                     int32_t frames_per_chunk, int32_t* out_frame_sel, void* workspace, size_t workspace_bytes,
                     hipStream_t stream) {
-    size_t need = 0;
-    int st = rc_retrieve_workspace_size(n_bank, n_query, k, &need);
-    if (st != REVISIT_OK) return st;
-    if (!(finite(E) && E > 0.0f)) return fail(REVISIT_ERR_PARAM, "retrieve_chunks: E must be finite and > 0");
-    if (!finite(w_v) || !finite(tau_c) || !finite(tau_v))
-        return fail(REVISIT_ERR_PARAM, "retrieve_chunks: w_v, tau_c and tau_v must be finite");
-    if (out_frame_sel && (frames_per_chunk < 1 || (int64_t)k * frames_per_chunk > (1 << 20)))
-        return fail(REVISIT_ERR_PARAM, "retrieve_chunks: frames_per_chunk=%d invalid", frames_per_chunk);
-    if (n_query == 0) return REVISIT_OK;
-    if (!query_c2w || !query_chunk || !out_idx || !out_count || (n_bank > 0 && !bank_c2w))
-        return fail(REVISIT_ERR_NULL, "retrieve_chunks: required pointer is NULL");
-    // the scan reads the pose columns it needs as 8-byte pairs
-    if (!aligned(bank_c2w, 8)) return fail(REVISIT_ERR_SHAPE, "retrieve_chunks: bank_c2w must be 8-byte aligned");
-    revisit::RetrieveArgs a;
-    a.bank_c2w = bank_c2w;
-    a.n_bank = n_bank;
-    a.query_c2w = query_c2w;
-    a.query_chunk = query_chunk;
-    a.n_query = n_query;
-    a.E = (double)E;
-    a.w_v = (double)w_v;
-    a.tau_c = (double)tau_c;
-    a.cos_tau_v = cos((double)tau_v);
-    // above (tau_c E)^2 (1 + 1e-9) the definition's sqrt(x) / E exceeds tau_c: its two roundings move it by
-    // 2^-52 of its value. fp32 tau_c and E keep the square between 1e-180 and 1e154 unless it is 0.
-    a.reach2 = (a.tau_c * a.E) * (a.tau_c * a.E) * (1.0 + 1e-9);
-    a.delta = delta;
-    a.first_candidate = first_candidate;
-    a.k = k;
-    a.out_idx = out_idx;
-    a.out_score = out_score;
-    a.out_count = out_count;
-    a.frames_per_chunk = frames_per_chunk;
-    a.out_frame_sel = out_frame_sel;
-    a.n_seg = revisit::retrieve_segments(n_bank);
-    a.seg_s = nullptr;
-    a.seg_j = nullptr;
-    st = check_workspace("retrieve_chunks", need, workspace, workspace_bytes);
-    if (st != REVISIT_OK) return st;
-    if (a.n_seg > 0) {
-        a.seg_s = static_cast<double*>(workspace);
-        a.seg_j = reinterpret_cast<int32_t*>(a.seg_s + (size_t)a.n_seg * n_query * k);
-    }
-    return launched(revisit::launch_retrieve(a, stream), "retrieve_chunks");
+    return revisit::retrieve_with_slots("retrieve_chunks", bank_c2w, n_bank, query_c2w, query_chunk, n_query, E, w_v, tau_c,
+                                        tau_v, delta, first_candidate, k, out_idx, out_score, out_count, frames_per_chunk,
+                                        out_frame_sel, nullptr, workspace, workspace_bytes, stream);
 }
 
 int rc_retrieve_workspace_size(int32_t n_bank, int32_t n_query, int32_t k, size_t* bytes) {
@@ -491,7 +506,7 @@ int pack_retrieved_kv(const void* store_k, const void* store_v, const int32_t* s
     if (!aligned(store_k, 16) || !aligned(store_v, 16) || !aligned(cache_k, 16) || !aligned(cache_v, 16) ||
         !aligned(sel, 4) || !aligned(store_pos, 4))
         return fail(REVISIT_ERR_SHAPE, "pack_retrieved_kv: store and cache must be 16-byte aligned, sel and store_pos 4-byte");
-    revisit::KvPackArgs a;
+    revisit::KvPackArgs a{};
     a.store_k = store_k;
     a.store_v = store_v;
     a.store_pos = store_pos;

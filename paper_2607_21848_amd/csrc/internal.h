@@ -21,6 +21,35 @@ __device__ inline unsigned xcd_item(unsigned block, unsigned n_items) {
     return (block % kXcds) * per_xcd + block / kXcds;
 }
 
+// The streaming driver's layout tables of chunk n, from its retrieval result:
+// the ring slot of every part (in layout order), the KV frame slot table
+// (retrieved frames 0..F-1 when a chunk was retrieved, -1 elsewhere) and the
+// reprojection's source frames (the retrieved chunk's frames in the ring, or
+// -1).
+constexpr int kStreamMaxParts = 5;
+struct StreamSlotsArgs {
+    int32_t n, F, capacity;
+    int32_t n_parts;
+    int32_t ret_part;  // index of the retrieved / extension part, -1 if absent
+    int32_t has_ret;
+    int32_t part_chunk[kStreamMaxParts];  // chunk of every other part
+    int32_t* part_slot;  // [n_parts] ring slots in layout order
+    int32_t* kv_slot;    // [n_parts * F]
+    int32_t* src_sel;    // [F]
+};
+__device__ inline int stream_ring_slot(int m, int capacity) { return m == 0 ? 0 : 1 + (m - 1) % (capacity - 1); }
+// Written by `threads` threads, this one being tid; count and idx are the retrieval's.
+__device__ inline void write_stream_slots(const StreamSlotsArgs& a, int count, int idx, int tid, int threads) {
+    const bool retrieved = a.has_ret && count > 0;
+    const int j = retrieved ? idx : a.n - 3;
+    for (int e = tid; e < a.n_parts * a.F; e += threads) {
+        const int i = e / a.F, f = e - i * a.F;
+        a.kv_slot[e] = (retrieved && i == a.ret_part) ? f : -1;
+        if (f == 0) a.part_slot[i] = stream_ring_slot(i == a.ret_part ? j : a.part_chunk[i], a.capacity);
+    }
+    for (int f = tid; f < a.F; f += threads) a.src_sel[f] = retrieved ? stream_ring_slot(j, a.capacity) * a.F + f : -1;
+}
+
 struct RetrieveArgs {
     const float* bank_c2w;
     int32_t n_bank;
@@ -41,7 +70,17 @@ struct RetrieveArgs {
     int32_t n_seg;
     double* seg_s;
     int32_t* seg_j;
+    // streaming driver (one query): the layout tables are written with the result
+    int32_t with_slots;
+    StreamSlotsArgs slots;
 };
+// retrieve_chunks with the layout tables of the streaming driver's chunk (slots,
+// nullable, one query) written by the same launch (capi.cpp)
+int retrieve_with_slots(const char* fn, const float* bank_c2w, int32_t n_bank, const float* query_c2w,
+                        const int32_t* query_chunk, int32_t n_query, float E, float w_v, float tau_c, float tau_v,
+                        int32_t delta, int32_t first_candidate, int32_t k, int32_t* out_idx, float* out_score,
+                        int32_t* out_count, int32_t frames_per_chunk, int32_t* out_frame_sel, const StreamSlotsArgs* slots,
+                        void* workspace, size_t workspace_bytes, hipStream_t stream);
 int32_t retrieve_segments(int32_t n_bank);
 size_t retrieve_workspace_bytes(int32_t n_bank, int32_t n_query, int32_t k);
 hipError_t launch_retrieve(const RetrieveArgs& a, hipStream_t stream);
@@ -140,6 +179,15 @@ struct KvPackArgs {
     int32_t D;
     int32_t n_t;
     double theta;
+    // streaming driver (fresh_k nullable): the last slot's chunk comes from
+    // fresh_k, fresh_v [L][T][H][D] instead of the store, is not rotated, and is
+    // written to store chunk fresh_slot (of keep_k, keep_v, the store itself; no
+    // other slot reads that chunk) as well as to its cache slot
+    const void* fresh_k;
+    const void* fresh_v;
+    void* keep_k;
+    void* keep_v;
+    int32_t fresh_slot;
 };
 int64_t kvpack_blocks(const KvPackArgs& a);
 hipError_t launch_kvpack(const KvPackArgs& a, hipStream_t stream);
@@ -160,19 +208,7 @@ struct StreamCommitArgs {
 };
 hipError_t launch_stream_commit(const StreamCommitArgs& a, hipStream_t stream);
 
-constexpr int kStreamMaxParts = 5;
-struct StreamSlotsArgs {
-    int32_t n, F, capacity;
-    int32_t n_parts;
-    int32_t ret_part;  // index of the retrieved / extension part, -1 if absent
-    int32_t has_ret;
-    int32_t part_chunk[kStreamMaxParts];  // chunk of every other part
-    const int32_t* ret_idx;
-    const int32_t* ret_count;
-    int32_t* part_slot;  // [n_parts] ring slots in layout order
-    int32_t* kv_slot;    // [n_parts * F]
-    int32_t* src_sel;    // [F]
-};
+// the tables where there is no retrieval (chunk 0)
 hipError_t launch_stream_slots(const StreamSlotsArgs& a, hipStream_t stream);
 hipError_t launch_pool_depth(const float* depth, int64_t n_tokens, int32_t h, int32_t w, int32_t p, float* out,
                              hipStream_t stream);

@@ -75,14 +75,16 @@ __global__ __launch_bounds__(kBlock) void kvpack_kernel(KvPackArgs a, int32_t pa
     const int ls = unit >> 1;
     const int slot = ls % a.n_sel;
     const int layer = ls / a.n_sel;
-    const int j = a.sel[slot];
+    const bool fresh = a.fresh_k && slot == a.n_sel - 1;  // uniform per block
+    const int j = fresh ? a.fresh_slot : a.sel[slot];
     if (j < 0 || j >= a.n_store) return;  // empty slot: left as it is (uniform exit)
 
     const int64_t row_elems = (int64_t)a.H * a.D;
     const int64_t chunk_elems = (int64_t)a.T * row_elems;
     const int64_t chunk_vecs = chunk_elems * ESIZE / 16;
-    const uint8_t* src = static_cast<const uint8_t*>(kv ? a.store_v : a.store_k) +
-                         ((int64_t)layer * a.n_store + j) * chunk_elems * ESIZE;
+    const int64_t kept = ((int64_t)layer * a.n_store + j) * chunk_elems * ESIZE;  // chunk j in the store
+    const uint8_t* src = fresh ? static_cast<const uint8_t*>(kv ? a.fresh_v : a.fresh_k) + layer * chunk_elems * ESIZE
+                               : static_cast<const uint8_t*>(kv ? a.store_v : a.store_k) + kept;
     uint8_t* dst = static_cast<uint8_t*>(kv ? a.cache_v : a.cache_k) +
                    ((int64_t)layer * a.cache_rows + a.dst_row0 + (int64_t)slot * a.T) * row_elems * ESIZE;
     const u32x4* s4 = reinterpret_cast<const u32x4*>(src);
@@ -96,7 +98,7 @@ __global__ __launch_bounds__(kBlock) void kvpack_kernel(KvPackArgs a, int32_t pa
         buf[i] = v < chunk_vecs ? __builtin_nontemporal_load(s4 + v) : u32x4{0, 0, 0, 0};
     }
 
-    const bool rotate = kv == 0 && a.n_t > 0;
+    const bool rotate = kv == 0 && a.n_t > 0 && !fresh;
     if (rotate) {  // uniform per block
         if (tid < a.n_t) {
             const int64_t pos_j = a.store_pos ? (int64_t)a.store_pos[j] : (int64_t)a.F * j;
@@ -149,6 +151,14 @@ __global__ __launch_bounds__(kBlock) void kvpack_kernel(KvPackArgs a, int32_t pa
     for (int i = 0; i < kVecsPerThread; ++i) {
         const int64_t v = v0 + (int64_t)i * kBlock;
         if (v < chunk_vecs) __builtin_nontemporal_store(buf[i], d4 + v);
+    }
+    if (fresh) {
+        u32x4* k4 = reinterpret_cast<u32x4*>(static_cast<uint8_t*>(kv ? a.keep_v : a.keep_k) + kept);
+#pragma unroll
+        for (int i = 0; i < kVecsPerThread; ++i) {
+            const int64_t v = v0 + (int64_t)i * kBlock;
+            if (v < chunk_vecs) __builtin_nontemporal_store(buf[i], k4 + v);
+        }
     }
 }
 

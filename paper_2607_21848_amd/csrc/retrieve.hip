@@ -339,8 +339,9 @@ __device__ __forceinline__ void finish(const RetrieveArgs& a, Shared& sh, int qi
         if (a.out_score) a.out_score[(size_t)qi * a.k + tid] = INFINITY;
     }
     if (tid == 0) a.out_count[qi] = count;
+    if (a.out_frame_sel || a.with_slots) __syncthreads();  // out_j
+    if (a.with_slots) write_stream_slots(a.slots, count, count > 0 ? sh.out_j[0] : -1, tid, blockDim.x);
     if (a.out_frame_sel) {
-        __syncthreads();  // out_j
         const int F = a.frames_per_chunk;
         const int total = a.k * F;
         for (int t = tid; t < total; t += blockDim.x)

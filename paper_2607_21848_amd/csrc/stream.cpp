@@ -56,7 +56,6 @@ struct rc_stream {
     int32_t* kv_slot;
     int32_t* src_sel;
     int32_t* store_pos;
-    int32_t* zero;
     void* workspace;  // attention key split and retrieval scratch of the largest step
     size_t workspace_bytes;
     // the last step's layout
@@ -91,7 +90,7 @@ void release(rc_stream* s) {
     void* bufs[] = {s->bank,      s->ring_depth, s->ring_c2w,   s->ring_K,      s->ring_k,    s->ring_v,
                     s->cache_k,   s->cache_v,    s->corr_uv,    s->corr_idx,    s->ret_idx,   s->ret_score,
                     s->ret_count, s->query_chunk, s->part_slot, s->kv_slot,     s->src_sel,   s->store_pos,
-                    s->zero,      s->workspace};
+                    s->workspace};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
 }
@@ -198,7 +197,7 @@ int rc_stream_create(const rc_stream_config* cfg, rc_stream** out) {
                     alloc(&s->ret_count, 16) && alloc(&s->query_chunk, 16) &&
                     alloc(&s->part_slot, revisit::kStreamMaxParts * 4) &&
                     alloc(&s->kv_slot, revisit::kStreamMaxParts * F * 4) && alloc(&s->src_sel, F * 4) &&
-                    alloc(&s->store_pos, C * 4) && alloc(&s->zero, 16) && alloc(&s->workspace, ws);
+                    alloc(&s->store_pos, C * 4) && alloc(&s->workspace, ws);
     if (!ok) {
         release(s);
         delete s;
@@ -212,9 +211,7 @@ int rc_stream_create(const rc_stream_config* cfg, rc_stream** out) {
         return revisit::fail_status(REVISIT_ERR_MEMORY, "rc_stream_create: out of host memory");
     }
     for (size_t i = 0; i < C; ++i) pos[i] = 4 * c.F;
-    const int32_t zero[4] = {0, 0, 0, 0};
-    const bool copied = hipMemcpy(s->store_pos, pos, C * 4, hipMemcpyHostToDevice) == hipSuccess &&
-                        hipMemcpy(s->zero, zero, 16, hipMemcpyHostToDevice) == hipSuccess;
+    const bool copied = hipMemcpy(s->store_pos, pos, C * 4, hipMemcpyHostToDevice) == hipSuccess;
     free(pos);
     if (!copied) {
         release(s);
@@ -263,20 +260,8 @@ int rc_stream_step(rc_stream* s, const float* depth, const float* c2w, const flo
                                  s->bank, s->query_chunk};
     hipError_t e = revisit::launch_stream_commit(ca, stream);
     if (e != hipSuccess) return revisit::fail_status(REVISIT_ERR_LAUNCH, "rc_stream_step: commit: %s", hipGetErrorString(e));
-    st = pack_retrieved_kv(k, v, nullptr, 1, s->zero, 1, 0, s->ring_k, s->ring_v, slot_n * T, C * T, c.layers, c.dtype,
-                           F, c.h, c.w, c.H, c.D, 0, 1.0f, stream);
-    if (st != REVISIT_OK) return st;
 
-    // retrieval (k = 1) over the resident history
-    if (n >= 1) {
-        const int32_t first = n - C + 2 > 1 ? n - C + 2 : 1;
-        st = retrieve_chunks(s->bank, n, s->bank + (size_t)n * 16, s->query_chunk, 1, c.E, c.w_v, c.tau_c, c.tau_v,
-                             c.delta, first, 1, s->ret_idx, s->ret_score, s->ret_count, 0, nullptr, s->workspace,
-                             s->workspace_bytes, stream);
-        if (st != REVISIT_OK) return st;
-    }
-
-    // the layout and its tables
+    // the layout, and retrieval (k = 1) over the resident history, which also writes the layout's tables
     Part parts[revisit::kStreamMaxParts];
     int32_t ret_part = -1;
     const int n_parts = layout(n, F, parts, &ret_part);
@@ -288,13 +273,19 @@ int rc_stream_step(rc_stream* s, const float* depth, const float* c2w, const flo
     sa.ret_part = ret_part;
     sa.has_ret = ret_part >= 0;
     for (int i = 0; i < n_parts; ++i) sa.part_chunk[i] = parts[i].chunk;
-    sa.ret_idx = s->ret_idx;
-    sa.ret_count = s->ret_count;
     sa.part_slot = s->part_slot;
     sa.kv_slot = s->kv_slot;
     sa.src_sel = s->src_sel;
-    e = revisit::launch_stream_slots(sa, stream);
-    if (e != hipSuccess) return revisit::fail_status(REVISIT_ERR_LAUNCH, "rc_stream_step: slots: %s", hipGetErrorString(e));
+    if (n >= 1) {
+        const int32_t first = n - C + 2 > 1 ? n - C + 2 : 1;
+        st = revisit::retrieve_with_slots("rc_stream_step", s->bank, n, s->bank + (size_t)n * 16, s->query_chunk, 1, c.E, c.w_v,
+                                          c.tau_c, c.tau_v, c.delta, first, 1, s->ret_idx, s->ret_score, s->ret_count, 0,
+                                          nullptr, &sa, s->workspace, s->workspace_bytes, stream);
+        if (st != REVISIT_OK) return st;
+    } else {
+        e = revisit::launch_stream_slots(sa, stream);
+        if (e != hipSuccess) return revisit::fail_status(REVISIT_ERR_LAUNCH, "rc_stream_step: slots: %s", hipGetErrorString(e));
+    }
 
     // correspondence of the current tokens into the retrieved chunk's frames, on the pooled maps
     const float* tgt_d = s->ring_depth + (size_t)slot_n * F * hw;
@@ -305,17 +296,44 @@ int rc_stream_step(rc_stream* s, const float* depth, const float* c2w, const flo
         if (st != REVISIT_OK) return st;
     }
 
-    // the packed cache: runs of consecutive positions in one call each; the current chunk unrotated.
-    // From chunk 2 on, part 0 is the anchor at rows 0..T-1 and positions 0..F-1, exactly as the
-    // previous step packed it (chunk 0 never leaves ring slot 0 and nothing else writes those rows),
-    // so it is not packed again.
+    // the packed cache: runs of consecutive positions in one launch each. The current chunk, the last
+    // part, is not rotated and comes from the caller; the same launch writes it to its ring slot, which
+    // no other part reads (the ring keeps the chunks n - capacity + 2 .. n - 1). From chunk 2 on, part 0
+    // is the anchor at rows 0..T-1 and positions 0..F-1, exactly as the previous step packed it (chunk 0
+    // never leaves ring slot 0 and nothing else writes those rows), so it is not packed again.
     for (int i0 = n >= 2 ? 1 : 0; i0 < n_parts;) {
         int i1 = i0 + 1;
-        while (i1 < n_parts && !parts[i1].current && !parts[i0].current && parts[i1].pos == parts[i1 - 1].pos + F) ++i1;
-        st = pack_retrieved_kv(s->ring_k, s->ring_v, s->store_pos, C, s->part_slot + i0, i1 - i0, parts[i0].pos,
-                               s->cache_k, s->cache_v, i0 * T, s->max_rows, c.layers, c.dtype, F, c.h, c.w, c.H, c.D,
-                               parts[i0].current ? 0 : c.rope_t_pairs, c.rope_theta, stream);
-        if (st != REVISIT_OK) return st;
+        while (i1 < n_parts && parts[i1].pos == parts[i1 - 1].pos + F) ++i1;
+        revisit::KvPackArgs pa{};
+        pa.store_k = s->ring_k;
+        pa.store_v = s->ring_v;
+        pa.store_pos = s->store_pos;
+        pa.n_store = C;
+        pa.sel = s->part_slot + i0;
+        pa.n_sel = i1 - i0;
+        pa.dst_pos = parts[i0].pos;
+        pa.cache_k = s->cache_k;
+        pa.cache_v = s->cache_v;
+        pa.dst_row0 = i0 * T;
+        pa.cache_rows = s->max_rows;
+        pa.n_layers = c.layers;
+        pa.esize = (int32_t)s->esize;
+        pa.F = F;
+        pa.T = T;
+        pa.H = c.H;
+        pa.D = c.D;
+        pa.n_t = c.rope_t_pairs;
+        pa.theta = (double)c.rope_theta;
+        if (parts[i1 - 1].current) {
+            pa.fresh_k = k;
+            pa.fresh_v = v;
+            pa.keep_k = s->ring_k;
+            pa.keep_v = s->ring_v;
+            pa.fresh_slot = slot_n;
+        }
+        // 16 KiB of the ring's five or more chunks per block: far below 2^31 blocks in any ring that fits
+        e = revisit::launch_kvpack(pa, stream);
+        if (e != hipSuccess) return revisit::fail_status(REVISIT_ERR_LAUNCH, "rc_stream_step: pack: %s", hipGetErrorString(e));
         i0 = i1;
     }
 

@@ -1,8 +1,8 @@
 // Token-depth pooling (pool_token_depth: the depth of Sec. 4.3 at token
 // resolution, kept per stored frame), and the device steps of the streaming
 // driver (stream.cpp) that are not one of the method's stages: putting a new
-// chunk into the history ring, and turning the retrieval result into the
-// cache layout's tables (Sec. 4.2, cache layout and loop-closure retrieval).
+// chunk into the history ring, and the cache layout's tables of a chunk without
+// retrieval (Sec. 4.2, cache layout and loop-closure retrieval).
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -68,24 +68,7 @@ __global__ __launch_bounds__(kBlock) void stream_commit_kernel(StreamCommitArgs 
     }
 }
 
-__device__ __forceinline__ int ring_slot_of(int m, int capacity) { return m == 0 ? 0 : 1 + (m - 1) % (capacity - 1); }
-
-// The layout's tables from the retrieval result, one thread: the ring slot of
-// every part (in layout order), the KV frame slot table (retrieved frames
-// 0..F-1 when a chunk was retrieved, -1 elsewhere) and the reprojection's
-// source frames (the retrieved chunk's frames in the ring, or -1).
-__global__ void stream_slots_kernel(StreamSlotsArgs a) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    const bool retrieved = a.has_ret && *a.ret_count > 0;
-    const int j = retrieved ? a.ret_idx[0] : a.n - 3;
-    for (int i = 0; i < a.n_parts; ++i) {
-        int m = a.part_chunk[i];
-        if (i == a.ret_part) m = j;
-        a.part_slot[i] = ring_slot_of(m, a.capacity);
-        for (int f = 0; f < a.F; ++f) a.kv_slot[i * a.F + f] = (retrieved && i == a.ret_part) ? f : -1;
-    }
-    for (int f = 0; f < a.F; ++f) a.src_sel[f] = retrieved ? ring_slot_of(j, a.capacity) * a.F + f : -1;
-}
+__global__ void stream_slots_kernel(StreamSlotsArgs a) { write_stream_slots(a, 0, -1, threadIdx.x, blockDim.x); }
 
 }  // namespace
 
