@@ -44,6 +44,13 @@ namespace {
 constexpr int kBlock = 128;  // measured 1-2% faster than 256 (and than 64, 512, 1024)
 constexpr int kMaxSrcLds = 64;  // source frames per problem
 constexpr int64_t kSmallLaunch = 512;  // token blocks below which a block takes one source
+// A large rotation launch of few sources: fewer sources than this, at least so
+// many tokens a frame and (token, source) pairs in all (100 MB of results); and
+// the blocks that rotation_source_kernel's launches should have.
+constexpr int kRotationSources = 8;
+constexpr int kRotationTokens = 512;
+constexpr int64_t kRotationPairs = 9000000;
+constexpr int64_t kRotationBlocks = 2048;
 
 // Mean of the p x p depth block of token (i, j): rows outer, columns inner.
 // P = 1 or 2: compile-time block; P = 0: runtime p.
@@ -482,14 +489,181 @@ __global__ __launch_bounds__(kBlock) void rotation_kernel(ReprojectArgs a) {
             i2 c = {code[0], code[1]};
             __builtin_nontemporal_store(c, reinterpret_cast<i2*>(a.out_idx + o));
         } else {
-            st_uv(reinterpret_cast<float2*>(a.out_uv) + o, uv[0]);
-            st_code(a.out_idx + o, code[0]);
+            // plain: the pieces of a line meet in the L2 (written past it one by one, half the
+            // sources of a 27 x 45 grid took 68 us where this takes 35: 300 problems, S 12)
+            reinterpret_cast<float2*>(a.out_uv)[o] = uv[0];
+            a.out_idx[o] = code[0];
             if (two) {
-                st_uv(reinterpret_cast<float2*>(a.out_uv) + o + 1, uv[1]);
-                st_code(a.out_idx + o + 1, code[1]);
+                reinterpret_cast<float2*>(a.out_uv)[o + 1] = uv[1];
+                a.out_idx[o + 1] = code[1];
             }
         }
     }
+}
+
+// homography_in_range of row r alone (all three rows of H in range: H is).
+__device__ __forceinline__ bool homography_row_in_range(const double* H, int r) {
+    bool ok = true, neg_zero = r < 2;
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+        const double m = fabs(H[e]);
+        ok = ok && (H[e] == 0.0 || (m >= 0x1p-200 && m <= 0x1p200));
+        neg_zero = neg_zero && H[e] == 0.0 && signbit(H[e]);
+    }
+    return ok && !neg_zero;
+}
+
+// Row r of the homography of source frame f for target frame bt.
+template <int P>
+__device__ __forceinline__ void homography_row(const ReprojectArgs& a, int bt, int f, int r, double* H) {
+    const double pd = (double)(P > 0 ? P : a.p);
+    const float* Mt = a.tgt_c2w + (size_t)bt * 16;
+    const float* Ms = a.src_c2w + (size_t)f * 16;
+    const float* Kt = a.tgt_K + (size_t)bt * 4;
+    const float* Ks = a.src_K + (size_t)f * 4;
+    const double fxt = per_token<P>(Kt[0], pd), fyt = per_token<P>(Kt[1], pd);
+    const double cxt = per_token<P>(Kt[2], pd), cyt = per_token<P>(Kt[3], pd);
+    const double fs = r < 2 ? per_token<P>(Ks[r], pd) : 0.0, cs = r < 2 ? per_token<P>(Ks[2 + r], pd) : 0.0;
+    double m[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const double t0 = (double)Mt[c], t1 = (double)Mt[4 + c], t2 = (double)Mt[8 + c];
+        const double a2 = ((double)Ms[2] * t0 + (double)Ms[6] * t1) + (double)Ms[10] * t2;
+        const double ar = ((double)Ms[r] * t0 + (double)Ms[4 + r] * t1) + (double)Ms[8 + r] * t2;
+        m[c] = r < 2 ? fs * ar + cs * a2 : a2;
+    }
+    H[0] = m[0] / fxt;
+    H[1] = m[1] / fyt;
+    H[2] = (m[2] - H[0] * cxt) - H[1] * cyt;
+}
+
+// Both tokens of the pair at (row i, column j) of a frame: u^ and codes.
+template <bool kShared>
+__device__ __forceinline__ void rotate_pair(const ReprojectArgs& a, const double* H, int i, int j, float2* uv, int* code) {
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+        const double ux = (double)j + 0.5, uy = (double)i + 0.5;
+        const double v0 = (H[0] * ux + H[1] * uy) + H[2];
+        const double v1 = (H[3] * ux + H[4] * uy) + H[5];
+        const double v2 = (H[6] * ux + H[7] * uy) + H[8];
+        double uhx, uhy;
+        if constexpr (kShared) {
+            const double y = 1.0 / v2;
+            uhx = quotient_from_reciprocal(v0, v2, y);
+            uhy = quotient_from_reciprocal(v1, v2, y);
+        } else {
+            uhx = v0 / v2;
+            uhy = v1 / v2;
+        }
+        const bool front = v2 > 0.0;
+        const bool on_grid = front && uhx >= 0.0 && uhx < (double)a.w && uhy >= 0.0 && uhy < (double)a.h;
+        uv[g] = front ? make_float2((float)uhx, (float)uhy) : make_float2(NAN, NAN);
+        code[g] = on_grid ? (int)uhy * a.w + (int)uhx : (front ? -3 : -2);
+        if (++j == a.w) {
+            j = 0;
+            ++i;
+        }
+    }
+}
+
+// The same for one (source, target frame) pair per block, `chunk` pairs of
+// tokens, `chunks` blocks per frame: three lanes form the rows of H, and
+// the block writes one contiguous range with plain stores. Taken where the
+// launch above would have too few blocks (16 problems of 30 x 52 tokens and 6
+// sources: 8.3 -> 5.9 us; of 8 x 12 and 12: 9.6 -> 4.3), and for large
+// launches of few sources, whose blocks above spend a long time on S
+// homographies for S writes and end lines in the middle: 1024 problems of 30 x 52
+// and 6 sources 89 -> 78 us (345 MB, 4.4 TB/s; stores alone reach 5.2 in this
+// order and 4.3 in the other). Between those, and from 8 sources on, the
+// kernel above is the faster (200 problems: 19.4 against 21.1 us; 512 problems of 45 x 80
+// and 12 sources: 154 against 164).
+struct RotationSplit {
+    int32_t chunk, chunks;
+};
+
+template <int P>
+__global__ __launch_bounds__(kBlock) void rotation_source_kernel(ReprojectArgs a, RotationSplit sp) {
+    const int hw = a.h * a.w;
+    const unsigned n_items = (unsigned)a.B * (unsigned)a.S * (unsigned)a.Tq * (unsigned)sp.chunks;
+    const unsigned item = (unsigned)__builtin_amdgcn_readfirstlane((int)xcd_item(blockIdx.x, n_items));
+    if (item >= n_items) return;  // grid padding (uniform, before the barrier)
+    // item = (b, source, t, chunk), the order of the outputs
+    const unsigned bst = item / (unsigned)sp.chunks;
+    const int ch = (int)(item - bst * (unsigned)sp.chunks);
+    const int bs = (int)(bst / (unsigned)a.Tq);
+    const int b = bs / a.S;
+    const int bt = b * a.Tq + (int)(bst - (unsigned)bs * (unsigned)a.Tq);
+
+    __shared__ double sh_H[9];
+    __shared__ int sh_status[3], sh_wide[3];
+    if (threadIdx.x < 3) {
+        const int r = threadIdx.x;
+        int f = bs;
+        if (a.src_sel) {
+            f = a.src_sel[bs];
+            if (f < 0 || f >= a.n_src) f = -1;
+        }
+        int status = -5, wide = 0;
+        if (f >= 0) {
+            const float* Mt = a.tgt_c2w + (size_t)bt * 16;
+            const float* Ms = a.src_c2w + (size_t)f * 16;
+            status = Mt[3] == Ms[3] && Mt[7] == Ms[7] && Mt[11] == Ms[11] ? 0 : -6;
+            double H[3];
+            homography_row<P>(a, bt, f, r, H);
+            wide = !homography_row_in_range(H, r);
+            for (int c = 0; c < 3; ++c) sh_H[3 * r + c] = H[c];
+        }
+        sh_status[r] = status;
+        sh_wide[r] = wide;
+    }
+    __syncthreads();
+    const size_t o0 = (size_t)bst * hw;
+    // pair k holds tokens 2 k - lead and 2 k - lead + 1: an even element index
+    const int lead = (int)(o0 & 1);
+    const int k_end = min((ch + 1) * sp.chunk, (hw + lead + 1) / 2);
+    int k = ch * sp.chunk + (int)threadIdx.x;
+    // row and column of the pair, stepped along (column -1: the token before the first, not stored)
+    int i = max(2 * k - lead, 0) / a.w;
+    int j = 2 * k - lead - i * a.w;
+    const int di = 2 * kBlock / a.w, dj = 2 * kBlock - di * a.w;
+    const int none = sh_status[0];
+    double H[9];
+#pragma unroll
+    for (int e = 0; e < 9; ++e) H[e] = sh_H[e];
+    auto pairs = [&](auto evaluate) __attribute__((always_inline)) {
+        for (; k < k_end; k += kBlock) {
+            float2 uv[2] = {make_float2(NAN, NAN), make_float2(NAN, NAN)};
+            int code[2] = {none, none};
+            evaluate(uv, code);
+            const int tok = 2 * k - lead;
+            const bool first = tok >= 0, second = tok + 1 < hw;
+            const size_t o = o0 + tok;
+            if (first && second && a.paired) {
+                typedef float f4 __attribute__((ext_vector_type(4)));
+                typedef int i2 __attribute__((ext_vector_type(2)));
+                *reinterpret_cast<f4*>(a.out_uv + 2 * o) = f4{uv[0].x, uv[0].y, uv[1].x, uv[1].y};
+                *reinterpret_cast<i2*>(a.out_idx + o) = i2{code[0], code[1]};
+            } else {
+                if (first) {
+                    reinterpret_cast<float2*>(a.out_uv)[o] = uv[0];
+                    a.out_idx[o] = code[0];
+                }
+                if (second) {
+                    reinterpret_cast<float2*>(a.out_uv)[o + 1] = uv[1];
+                    a.out_idx[o + 1] = code[1];
+                }
+            }
+            i += di;
+            j += dj;
+            if (j >= a.w) {
+                j -= a.w;
+                ++i;
+            }
+        }
+    };
+    if (none != 0) pairs([](float2*, int*) {});
+    else if (sh_wide[0] | sh_wide[1] | sh_wide[2]) pairs([&](float2* uv, int* code) { rotate_pair<false>(a, H, i, j, uv, code); });
+    else pairs([&](float2* uv, int* code) { rotate_pair<true>(a, H, i, j, uv, code); });
 }
 
 }  // namespace
@@ -525,7 +699,22 @@ hipError_t launch_rotation(const ReprojectArgs& a, hipStream_t stream) {
     if (a.B == 0 || a.Tq == 0 || a.S == 0 || hw == 0) return hipSuccess;
     const int64_t blocks = (int64_t)((hw + 2 * kBlock - 1) / (2 * kBlock)) * a.B * a.Tq;
     if (blocks > INT32_MAX - kXcds) return hipErrorInvalidValue;
-    const dim3 grid(xcd_grid((unsigned)blocks)), block(kBlock);
+    const dim3 block(kBlock);
+    const int64_t frames = (int64_t)a.B * a.S * a.Tq;  // (problem, source, target frame)
+    const bool large = a.S < kRotationSources && hw >= kRotationTokens && frames * hw >= kRotationPairs;
+    const int64_t max_chunks = (hw / 2 + kBlock) / kBlock;  // blocks of one pair per thread
+    if ((blocks < kSmallLaunch || large) && frames * max_chunks <= INT32_MAX / 2) {
+        const int64_t want = (kRotationBlocks + frames - 1) / frames;
+        RotationSplit sp;
+        sp.chunks = (int32_t)(want < max_chunks ? want : max_chunks);
+        sp.chunk = (hw / 2 + 1 + sp.chunks - 1) / sp.chunks;
+        const dim3 grid(xcd_grid((unsigned)(frames * sp.chunks)));
+        if (a.p == 2) hipLaunchKernelGGL((rotation_source_kernel<2>), grid, block, 0, stream, a, sp);
+        else if (a.p == 1) hipLaunchKernelGGL((rotation_source_kernel<1>), grid, block, 0, stream, a, sp);
+        else hipLaunchKernelGGL((rotation_source_kernel<0>), grid, block, 0, stream, a, sp);
+        return hipGetLastError();
+    }
+    const dim3 grid(xcd_grid((unsigned)blocks));
     if (a.p == 2) hipLaunchKernelGGL((rotation_kernel<2>), grid, block, 0, stream, a);
     else if (a.p == 1) hipLaunchKernelGGL((rotation_kernel<1>), grid, block, 0, stream, a);
     else hipLaunchKernelGGL((rotation_kernel<0>), grid, block, 0, stream, a);
