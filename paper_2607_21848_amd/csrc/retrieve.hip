@@ -6,8 +6,8 @@
 // registers, together with the best pair it had to drop. The gates leave few
 // candidates (a loop passes a place a few times), so the workgroup collects
 // the lanes' pairs in LDS and each pair's rank is the number of pairs before
-// it: no rounds of reductions. Only when more than kRankMax are left does each
-// wave first reduce its lanes' lists to its k best with a butterfly argmin per
+// it: no rounds of reductions. Only when there are many does each wave first
+// reduce its lanes' lists to its k best with a butterfly argmin per
 // result. Pairs before the best dropped one are certainly the first ones; if
 // that is fewer than k, the bank is scanned again for the pairs after them
 // (each scan settles at least kLane). Scores are computed with exactly the
@@ -26,9 +26,10 @@
 // Measured per call on the device (a captured graph of calls), before (one wave per query scanning in
 // turn, sorted lists of up to 32 pairs in registers, k butterfly rounds per
 // wave and again per query) and now: 200 entries, k 4: 4.9 -> 4.3 us; 3000,
-// k 4: 17.3 -> 8.8; 8000, k 32: 79 -> 10.5; 10^6, 4 queries, k 8: 65 -> 28;
-// 113615, 9 queries, k 26: 697 -> 32; 2 10^6, 16 queries, k 32: 5550 -> 170;
-// 2^23, k 4: 109 -> 107 (5 TB/s).
+// k 4: 17.3 -> 8.6; 8000, k 32: 78 -> 11; 10^6, 4 queries, k 8: 62 -> 25;
+// 113615, 9 queries, k 26: 696 -> 30; 2 10^6, 16 queries, k 32: 5500 -> 156;
+// 2^23, k 4: 109 -> 102 (5.2 TB/s), and 109 -> 113 where 3% of it are in reach;
+// 10^6 entries all in reach, k 4: 34.4 -> 30.0.
 
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -50,11 +51,11 @@ constexpr int kUnroll = 4;                             // bank entries in flight
 constexpr int kLane = 4;                               // best pairs a lane keeps
 constexpr int kMaxK = 32;
 constexpr int kRankLanes = 8;                          // lanes that count one pair's rank
-// Largest number of pairs ranked by counting without a reduction first: m^2
-// comparisons over the workgroup, where a wave's reduction takes k dependent
-// butterflies of 18 lane exchanges each. Up to 32 pairs of each wave are left
-// after that.
-constexpr int kRankMax = 256;
+// Pairs are ranked by counting without a reduction first when that takes each
+// thread at most kRankCost comparisons per result wanted (16 comparisons take
+// about as long as one result's round of the waves' reductions, 18 dependent
+// lane exchanges).
+constexpr int kRankCost = 16;
 
 // (s1, j1) strictly before (s2, j2): smaller score, then smaller index.
 __device__ __forceinline__ bool before(double s1, int j1, double s2, int j2) {
@@ -78,22 +79,28 @@ struct LaneTop {
         ds = INFINITY;
         dj = INT32_MAX;
     }
-    // sorted insertion: the new pair moves up past those it is before; what
-    // is left over at the end is dropped
+    // sorted insertion: slot i takes the new pair if it belongs exactly there,
+    // or the pair above it if the new one goes higher up; kDrop: the pair that
+    // is left over is noted
+    template <bool kDrop>
     __device__ __forceinline__ void offer(double ns, int nj) {
-#pragma unroll
-        for (int i = 0; i < kLane; ++i) {
-            const bool here = before(ns, nj, s[i], j[i]);
-            const double os = s[i];
-            const int oj = j[i];
-            s[i] = here ? ns : os;
-            j[i] = here ? nj : oj;
-            ns = here ? os : ns;
-            nj = here ? oj : nj;
+        const bool in = before(ns, nj, s[kLane - 1], j[kLane - 1]);
+        if constexpr (kDrop) {
+            const double os = in ? s[kLane - 1] : ns;
+            const int oj = in ? j[kLane - 1] : nj;
+            if (before(os, oj, ds, dj)) {
+                ds = os;
+                dj = oj;
+            }
         }
-        if (before(ns, nj, ds, dj)) {
-            ds = ns;
-            dj = nj;
+        if (!in) return;
+#pragma unroll
+        for (int i = kLane - 1; i >= 0; --i) {
+            if (before(ns, nj, s[i], j[i])) {
+                const bool here = i == 0 || before(s[i > 0 ? i - 1 : 0], j[i > 0 ? i - 1 : 0], ns, nj);
+                s[i] = here ? ns : s[i > 0 ? i - 1 : 0];
+                j[i] = here ? nj : j[i > 0 ? i - 1 : 0];
+            }
         }
     }
     __device__ __forceinline__ void pop() {
@@ -131,12 +138,15 @@ struct Shared {
     int pairs, kept;
 };
 
+// kMany: k > kLane, so that pairs may be dropped and the scan repeated (k
+// results at most kLane of a lane otherwise).
+//
 // The k first pairs of everything that scan(offer) offers, in order: calls
 // put(r, s, j) for result r in one thread and returns the number found (the
 // same in every thread). scan is called with offer(s, j), once per pass over
 // the data, by every thread for its share. Every thread of the workgroup
 // (whole waves) calls this together.
-template <class Scan, class Put>
+template <bool kMany, class Scan, class Put>
 __device__ __forceinline__ int first_k(Shared& sh, int k, Scan scan, Put put) {
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
@@ -151,7 +161,7 @@ __device__ __forceinline__ int first_k(Shared& sh, int k, Scan scan, Put put) {
         top.clear();
         if (tid == 0) sh.pairs = sh.kept = 0;
         scan([&](double s, int j) {
-            if (before(after_s, after_j, s, j)) top.offer(s, j);
+            if (!kMany || before(after_s, after_j, s, j)) top.template offer<kMany>(s, j);
         });
         __syncthreads();  // the counters are cleared, the last pass's results are read
 
@@ -169,7 +179,7 @@ __device__ __forceinline__ int first_k(Shared& sh, int k, Scan scan, Put put) {
             sh.drop_j[wave] = INT32_MAX;
         }
         base = __shfl(base, 0);
-        if (__any(top.dj != INT32_MAX)) {
+        if (kMany && __any(top.dj != INT32_MAX)) {
             wave_first(top.ds, top.dj);
             if (lane == 0) {
                 sh.drop_s[wave] = top.ds;
@@ -179,7 +189,7 @@ __device__ __forceinline__ int first_k(Shared& sh, int k, Scan scan, Put put) {
         __syncthreads();
         const int need = k - done;
         int m = sh.pairs;
-        if (m <= kRankMax) {
+        if (m <= kMaxWaves * kMaxK && m * m <= (int)blockDim.x * kRankCost * need) {
 #pragma unroll
             for (int i = 0; i < kLane; ++i) {
                 if (top.j[i] != INT32_MAX) {
@@ -234,6 +244,13 @@ __device__ __forceinline__ int first_k(Shared& sh, int k, Scan scan, Put put) {
         }
         __syncthreads();
         const int found = min(m, need);
+        if constexpr (!kMany) {
+            if (tid < found) {
+                put(tid, sh.res_s[tid], sh.res_j[tid]);
+                sh.out_j[tid] = sh.res_j[tid];
+            }
+            return found;
+        }
 
         // the results before every dropped pair are certain
         double ds = INFINITY;
@@ -286,28 +303,16 @@ __device__ __forceinline__ PoseCols load_cols(const RetrieveArgs& a, int j) {
                     *reinterpret_cast<const float2*>(m + 10)};
 }
 
-// Score and gates of bank entry j (in the query's index range) for query qp
-// (Eq. retrieval); offers the pair when admissible. Most entries are out of
-// reach: those are told by the squared distance alone (a.reach2 is
-// (tau_c E)^2 with a margin that no rounding of the definition's square root
-// and quotient can bridge), without the square root and the division.
-template <class Offer>
-__device__ __forceinline__ void score_entry(const RetrieveArgs& a, int j, const PoseCols& m, const QueryPose& qp,
-                                            Offer& offer) {
-    const double dx = (double)m.r0.y - qp.cx;
-    const double dy = (double)m.r1.y - qp.cy;
-    const double dz = (double)m.r2.y - qp.cz;
-    const double x = dx * dx + dy * dy + dz * dz;
-    const double al = (double)m.r0.x * qp.vx + (double)m.r1.x * qp.vy + (double)m.r2.x * qp.vz;
-    if (x > a.reach2 || !(al >= a.cos_tau_v)) return;
-    const double d = sqrt(x) / a.E;
-    const double s = d + a.w_v * (1.0 - al);
-    if (d <= a.tau_c) offer(s, j);
-}
-
-// Bank entries [begin, end), kUnroll per lane at a time, waves in turn: all
-// loads of a batch are issued before any is scored (an index past the end is
-// clamped for the load and not scored).
+// Bank entries [begin, end) of the query's index range, kUnroll per lane at a
+// time, waves in turn (each wave its own contiguous part: 2^23 entries 108 us
+// instead of 102): all loads of a batch are issued before any is scored (an
+// index past the end is clamped for the load and not scored), and admissible
+// pairs are offered. Most entries are out of reach: those are told by the
+// squared distance alone (a.reach2 is (tau_c E)^2 with a margin that no rounding
+// of the definition's square root and quotient can bridge), and a batch with
+// nothing in reach needs neither; otherwise the batch's square roots and
+// quotients are evaluated together (one after the other behind a branch each
+// they cost 10% where a few per cent of a bank of 2^23 are in reach).
 template <class Offer>
 __device__ __forceinline__ void scan_bank(const RetrieveArgs& a, int begin, int end, const QueryPose& qp, Offer& offer) {
     const int lane = threadIdx.x & (kWave - 1);
@@ -318,9 +323,29 @@ __device__ __forceinline__ void scan_bank(const RetrieveArgs& a, int begin, int 
         PoseCols m[kUnroll];
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) m[u] = load_cols(a, min(j0 + u * kWave, end - 1));
+        double x[kUnroll], al[kUnroll];  // squared distance, cosine
+        bool near[kUnroll], any = false;
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
-            if (j0 + u * kWave < end) score_entry(a, j0 + u * kWave, m[u], qp, offer);
+            const double dx = (double)m[u].r0.y - qp.cx;
+            const double dy = (double)m[u].r1.y - qp.cy;
+            const double dz = (double)m[u].r2.y - qp.cz;
+            x[u] = dx * dx + dy * dy + dz * dz;
+            al[u] = (double)m[u].r0.x * qp.vx + (double)m[u].r1.x * qp.vy + (double)m[u].r2.x * qp.vz;
+            near[u] = j0 + u * kWave < end && !(x[u] > a.reach2) && al[u] >= a.cos_tau_v;
+            any = any || near[u];
+        }
+        if (!__any(any)) continue;
+        double s[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const double d = sqrt(x[u]) / a.E;
+            s[u] = d + a.w_v * (1.0 - al[u]);
+            near[u] = near[u] && d <= a.tau_c;
+        }
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            if (near[u]) offer(s[u], j0 + u * kWave);
         }
     }
 }
@@ -350,11 +375,12 @@ __device__ __forceinline__ void finish(const RetrieveArgs& a, Shared& sh, int qi
 }
 
 // The whole bank for query blockIdx.x.
+template <bool kMany>
 __global__ __launch_bounds__(kMaxWaves * kWave) void retrieve_kernel(RetrieveArgs a) {
     __shared__ Shared sh;
     const int qi = blockIdx.x;
     const QueryPose qp = query_pose(a, qi);
-    const int count = first_k(
+    const int count = first_k<kMany>(
         sh, a.k, [&](auto offer) { scan_bank(a, qp.lo, qp.hi, qp, offer); },
         [&](int r, double s, int j) { put_result(a, qi, r, s, j); });
     finish(a, sh, qi, count);
@@ -364,6 +390,7 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void retrieve_kernel(RetrieveArg
 // seg_j [qi][seg][0 .. k), (INFINITY, INT32_MAX) past the admissible ones. The
 // queries of one segment are neighbours on one XCD, so its L2 serves the bank
 // to all but the first.
+template <bool kMany>
 __global__ __launch_bounds__(kSegWaves * kWave) void retrieve_segment_kernel(RetrieveArgs a) {
     __shared__ Shared sh;
     const unsigned n_items = (unsigned)a.n_seg * (unsigned)a.n_query;
@@ -379,17 +406,18 @@ __global__ __launch_bounds__(kSegWaves * kWave) void retrieve_segment_kernel(Ret
         a.seg_s[base + r] = s;
         a.seg_j[base + r] = j;
     };
-    const int count = first_k(sh, a.k, [&](auto offer) { scan_bank(a, begin, end, qp, offer); }, put);
+    const int count = first_k<kMany>(sh, a.k, [&](auto offer) { scan_bank(a, begin, end, qp, offer); }, put);
     if ((int)threadIdx.x >= count && (int)threadIdx.x < a.k) put(threadIdx.x, INFINITY, INT32_MAX);
 }
 
 // The results of query blockIdx.x from its n_seg * k segment results.
+template <bool kMany>
 __global__ __launch_bounds__(kMaxWaves * kWave) void retrieve_merge_kernel(RetrieveArgs a) {
     __shared__ Shared sh;
     const int qi = blockIdx.x;
     const size_t base = (size_t)qi * a.n_seg * a.k;
     const int n_cand = a.n_seg * a.k;
-    const int count = first_k(
+    const int count = first_k<kMany>(
         sh, a.k,
         [&](auto offer) {
             for (int c = threadIdx.x; c < n_cand; c += blockDim.x) {
@@ -418,19 +446,24 @@ size_t retrieve_workspace_bytes(int32_t n_bank, int32_t n_query, int32_t k) {
     return (size_t)n_seg * n_query * k * (sizeof(double) + sizeof(int32_t));
 }
 
-hipError_t launch_retrieve(const RetrieveArgs& a, hipStream_t stream) {
-    if (a.n_query == 0) return hipSuccess;
+template <bool kMany>
+static hipError_t launch_many(const RetrieveArgs& a, hipStream_t stream) {
     if (a.n_seg == 0) {
         // one batch of loads per lane where 16 waves suffice for that: 3000 entries took 17 us in one wave, 8.8 us in twelve
-        hipLaunchKernelGGL(retrieve_kernel, dim3(a.n_query), waves_for(a.n_bank, kUnroll * kWave), 0, stream, a);
+        hipLaunchKernelGGL(retrieve_kernel<kMany>, dim3(a.n_query), waves_for(a.n_bank, kUnroll * kWave), 0, stream, a);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(retrieve_segment_kernel, dim3(xcd_grid((unsigned)a.n_query * a.n_seg)), dim3(kSegWaves * kWave), 0,
+    hipLaunchKernelGGL(retrieve_segment_kernel<kMany>, dim3(xcd_grid((unsigned)a.n_query * a.n_seg)), dim3(kSegWaves * kWave), 0,
                        stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(retrieve_merge_kernel, dim3(a.n_query), waves_for((int64_t)a.n_seg * a.k, kWave), 0, stream, a);
+    hipLaunchKernelGGL(retrieve_merge_kernel<kMany>, dim3(a.n_query), waves_for((int64_t)a.n_seg * a.k, kWave), 0, stream, a);
     return hipGetLastError();
+}
+
+hipError_t launch_retrieve(const RetrieveArgs& a, hipStream_t stream) {
+    if (a.n_query == 0) return hipSuccess;
+    return a.k > kLane ? launch_many<true>(a, stream) : launch_many<false>(a, stream);
 }
 
 }  // namespace revisit
