@@ -263,7 +263,9 @@ int reproject_correspondence(const float* tgt_depth, const float* tgt_c2w, const
  *               shape and key_parts on the same device (items * P * 66.5 KiB
  *               when P > 1, else 0), 16-byte aligned; may be NULL / 0 when
  *               that size is 0. Too small: REVISIT_ERR_SHAPE; NULL while
- *               needed: REVISIT_ERR_NULL.
+ *               needed: REVISIT_ERR_NULL. With key_parts = 0 and fewer than 256
+ *               key tiles of 32 keys a smaller one, or none, is taken too: the
+ *               keys are then cut into as many parts as fit in it.
  */
 int biased_chunk_attention(const void* q, const void* k, const void* v, void* o,
                            float* lse, int32_t dtype,

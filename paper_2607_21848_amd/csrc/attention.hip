@@ -1406,6 +1406,22 @@ int32_t attention_bf16_key_parts(const AttentionArgs& a, int32_t cus) {
     return best;
 }
 
+int32_t attention_bf16_least_parts(const AttentionArgs& a, int32_t slots) {
+    // the fewest parts of at least 128 key tiles, four at most, that fill the last
+    // round of workgroups to 97 %; else one from four rounds on, else the most
+    constexpr int kMinTiles = 128, kMostParts = 4;
+    const int64_t items = (int64_t)((a.Lq + 127) / 128) * a.H * a.layers;
+    const int n_tiles = (a.Lk + kTK - 1) / kTK;
+    int largest = 1;
+    for (int p = 1; p <= kMostParts && (p == 1 || n_tiles / p >= kMinTiles); ++p) {
+        const int64_t units = items * p;
+        const int64_t rounds = (units + slots - 1) / slots;
+        if ((double)units >= 0.97 * (double)(rounds * slots)) return p;
+        largest = p;
+    }
+    return items >= 4 * (int64_t)slots ? 1 : largest;
+}
+
 size_t attention_bf16_workspace_bytes(const AttentionArgs& a, int32_t parts) {
     if (parts <= 1) return 0;
     const int64_t items = (int64_t)((a.Lq + 127) / 128) * a.H * a.layers;

@@ -355,7 +355,9 @@ int prepare_attention(const char* fn, const void* q, const void* k, const void* 
     return REVISIT_OK;
 }
 
-// The launch with the caller's workspace.
+// The launch with the caller's workspace. The automatic split takes what the
+// size query says, or, in a smaller workspace that holds at least the parts of
+// attention_bf16_least_parts (none for short key ranges), as many parts as fit.
 int run_attention(const char* fn, const revisit::AttentionArgs& a, int32_t dtype, int32_t key_parts, void* workspace,
                   size_t workspace_bytes, hipStream_t stream) {
     if (dtype == REVISIT_F32) return launched(revisit::launch_attention_f32(a, stream), fn);
@@ -363,6 +365,18 @@ int run_attention(const char* fn, const revisit::AttentionArgs& a, int32_t dtype
     size_t need = 0;
     int st = attention_parts(fn, a, key_parts, &parts, &need);
     if (st != REVISIT_OK) return st;
+    const bool usable = workspace && aligned(workspace, kWorkspaceAlign);
+    if (need > 0 && key_parts == 0 && (workspace_bytes < need || !usable)) {
+        int cus = 0;
+        const hipError_t e = device_compute_units(&cus);
+        if (e != hipSuccess) return fail(REVISIT_ERR_LAUNCH, "%s: device query failed: %s", fn, hipGetErrorString(e));
+        const size_t least = revisit::attention_bf16_workspace_bytes(a, revisit::attention_bf16_least_parts(a, 2 * cus));
+        if (least == 0 || (least <= workspace_bytes && usable)) {
+            const size_t have = usable ? workspace_bytes : 0;
+            while (parts > 1 && revisit::attention_bf16_workspace_bytes(a, parts) > have) --parts;
+            need = 0;  // what remains fits
+        }
+    }
     st = check_workspace(fn, need, workspace, workspace_bytes);
     if (st != REVISIT_OK) return st;
     return launched(revisit::launch_attention_bf16(a, parts, static_cast<float*>(workspace), stream), fn);

@@ -133,6 +133,9 @@ hipError_t launch_attention_f32(const AttentionArgs& a, hipStream_t stream);
 // (attention_bf16_workspace_bytes). attention_bf16_key_parts picks the
 // number of parts that should be fastest on `cus` compute units.
 int32_t attention_bf16_key_parts(const AttentionArgs& a, int32_t cus);
+// Parts whose workspace an automatic call has to bring at least, for `slots`
+// resident workgroups.
+int32_t attention_bf16_least_parts(const AttentionArgs& a, int32_t slots);
 size_t attention_bf16_workspace_bytes(const AttentionArgs& a, int32_t parts);
 hipError_t launch_attention_bf16(const AttentionArgs& a, int32_t parts, float* workspace, hipStream_t stream);
 

@@ -42,3 +42,22 @@ def test_merge_of_many_parts(parts):
 @pytest.mark.parametrize("frames", [1, 2, 5, 18])
 def test_automatic_split_of_short_ranges(frames):
     _check(_case(60, frames, 9, 16, min(frames, 3), 3, frames), 9, 16, 0)
+
+
+def test_automatic_split_in_a_smaller_workspace():
+    """Short key ranges need no workspace: the split takes what fits (equal to that many forced
+    parts, bit for bit). A long range that has always needed one is refused without it."""
+    q, k, v, slot, uv, idx = _case(140, 9, 13, 18, 3, 2, 9)
+    args = [dev(x, torch.bfloat16) for x in (q, k, v)] + [dev(slot), dev(uv), dev(idx)]
+    kw = dict(h=13, w=18, softmax_scale=128 ** -0.5, lam=1.0, sigma=2.0)
+    auto = rv.attention_workspace_size(torch.bfloat16, 140, k.shape[0], 2, 128) // (4 * 66560)
+    assert auto >= 3
+    for nbytes, parts in ((16, 1), (2 * 4 * 66560 - 1, 1), (3 * 4 * 66560, 3), (auto * 4 * 66560, auto)):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        got = rv.biased_chunk_attention(*args, **kw, workspace=ws)
+        want = rv.biased_chunk_attention(*args, **kw, key_parts=parts)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), (nbytes, parts)
+    long = [torch.zeros(n, 1, 128, dtype=torch.bfloat16, device="cuda") for n in (128, 8448, 8448)]
+    with pytest.raises(rv.RevisitError):
+        rv.biased_chunk_attention(*long, dev(np.full(1, -1, np.int32)), None, None, h=96, w=88, softmax_scale=0.1, lam=1.0,
+                                  sigma=1.0, workspace=torch.empty(16, dtype=torch.uint8, device="cuda"))
