@@ -1375,8 +1375,9 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttentionArgs a, KeySpl
 int32_t attention_bf16_key_parts(const AttentionArgs& a, int32_t cus) {
     // The number of parts with the least estimated time. The busiest compute
     // unit runs n = ceil(items P / cus) workgroups of ceil(tiles / P) key tiles,
-    // two at a time: 0.45 us a tile in company, 0.57 alone, 2 us for each further
-    // pair's start. A merge is a second launch (2.5 us) and 66.5 KB written and
+    // two at a time: 0.45 us a tile in company (less while the chip's places are
+    // under three quarters full: 296 items of 147 tiles, 109 us whole, would be put
+    // at 140), 0.57 alone, 2 us for each further pair's start. A merge is a second launch (2.5 us) and 66.5 KB written and
     // read back per workgroup (22 us per 1000). Fitted to 1100 timings (2 to 1700
     // items, 5 to 2025 tiles, 1 to 32 parts; 8% off on average); its choice is on
     // average 1.5% above the best of the measured parts. A rule that filled two
@@ -1396,7 +1397,9 @@ int32_t attention_bf16_key_parts(const AttentionArgs& a, int32_t cus) {
         if ((p > 4 || (p > 1 && a.layers > 1)) && units > kSplitUnits) break;
         const int64_t n = (units + cus - 1) / cus;
         const int64_t odd = n % 2, tiles = (n_tiles + p - 1) / p;
-        double us = (0.45 * (double)(n - odd) + 0.57 * (double)odd) * (double)tiles + 2.0 * (double)((n + 1) / 2);
+        const double full = (double)units / (double)(n * cus);
+        const double company = 0.45 - 0.38 * (full < 0.75 ? 0.75 - full : 0.0);
+        double us = (company * (double)(n - odd) + 0.57 * (double)odd) * (double)tiles + 2.0 * (double)((n + 1) / 2);
         us += 7.0 + (p > 1 ? 2.5 + 0.022 * (double)units : 0.0);
         if (us < 0.985 * best_us) {
             best = p;
