@@ -622,9 +622,11 @@ __global__ __launch_bounds__(kBlock) void rotation_source_kernel(ReprojectArgs a
     const int lead = (int)(o0 & 1);
     const int k_end = min((ch + 1) * sp.chunk, (hw + lead + 1) / 2);
     int k = ch * sp.chunk + (int)threadIdx.x;
-    // row and column of the pair, stepped along (column -1: the token before the first, not stored)
-    int i = max(2 * k - lead, 0) / a.w;
-    int j = 2 * k - lead - i * a.w;
+    // row and column of the pair's first token, stepped along (the one before token 0 is not
+    // stored: the last column of row -1, from where the steps below lead on like from any other)
+    const int tok0 = 2 * k - lead;
+    int i = tok0 < 0 ? -1 : tok0 / a.w;
+    int j = tok0 - i * a.w;
     const int di = 2 * kBlock / a.w, dj = 2 * kBlock - di * a.w;
     const int none = sh_status[0];
     double H[9];
