@@ -429,10 +429,15 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void retrieve_merge_kernel(Retri
     finish(a, sh, qi, count);
 }
 
-// Waves of a workgroup over n entries, `each` per wave.
-dim3 waves_for(int64_t n, int each) {
-    const int64_t w = (n + each - 1) / each;
-    return dim3((unsigned)(kWave * (w < 1 ? 1 : w > kMaxWaves ? kMaxWaves : w)));
+// Waves of a workgroup over n entries, `each` per wave, as many as a launch of
+// n_query workgroups has threads for: fewer than 2^32 (the runtime takes a larger
+// count modulo 2^32).
+dim3 waves_for(int64_t n, int each, int32_t n_query) {
+    const int64_t most = (((int64_t)1 << 32) - 1) / kWave / n_query;
+    int64_t w = (n + each - 1) / each;
+    w = w < kMaxWaves ? w : kMaxWaves;
+    w = w < most ? w : most;
+    return dim3((unsigned)(kWave * (w < 1 ? 1 : w)));
 }
 
 }  // namespace
@@ -450,14 +455,14 @@ template <bool kMany>
 static hipError_t launch_many(const RetrieveArgs& a, hipStream_t stream) {
     if (a.n_seg == 0) {
         // one batch of loads per lane where 16 waves suffice for that: 3000 entries took 17 us in one wave, 8.8 us in twelve
-        hipLaunchKernelGGL(retrieve_kernel<kMany>, dim3(a.n_query), waves_for(a.n_bank, kUnroll * kWave), 0, stream, a);
+        hipLaunchKernelGGL(retrieve_kernel<kMany>, dim3(a.n_query), waves_for(a.n_bank, kUnroll * kWave, a.n_query), 0, stream, a);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(retrieve_segment_kernel<kMany>, dim3(xcd_grid((unsigned)a.n_query * a.n_seg)), dim3(kSegWaves * kWave), 0,
                        stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(retrieve_merge_kernel<kMany>, dim3(a.n_query), waves_for((int64_t)a.n_seg * a.k, kWave), 0, stream, a);
+    hipLaunchKernelGGL(retrieve_merge_kernel<kMany>, dim3(a.n_query), waves_for((int64_t)a.n_seg * a.k, kWave, a.n_query), 0, stream, a);
     return hipGetLastError();
 }
 

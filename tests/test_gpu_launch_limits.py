@@ -1,0 +1,46 @@
+"""Calls of so many workgroups that one launch of one dimension (2^32 threads) does not hold them."""
+
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2607_21848_amd as rv
+from oracle import retrieval as ORT
+from tests.gpu_helpers import host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _give_back():
+    torch.cuda.empty_cache()
+    yield
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+
+
+def _poses(x, y):
+    m = torch.zeros(len(x), 4, 4, device="cuda")
+    m[:, range(4), range(4)] = 1.0
+    m[:, 0, 3], m[:, 1, 3] = x, y
+    return m
+
+
+@pytest.mark.parametrize("k", [1, 5])
+def test_retrieval_of_many_queries(k):
+    """2^22 + 5 queries over 4000 entries, which sixteen waves a query would scan."""
+    N, Q = 4000, (1 << 22) + 5
+    g = torch.Generator(device="cuda").manual_seed(k)
+    r = lambda n: 20 * torch.rand(n, generator=g, device="cuda")  # noqa: E731
+    bank, query = _poses(r(N), r(N)), _poses(r(Q), r(Q))
+    chunk = torch.full((Q,), N + 3, dtype=torch.int32, device="cuda")
+    kw = dict(E=20.0, w_v=0.5, tau_c=0.02, tau_v=1.0, delta=3, first_candidate=1, k=k)
+    print(f"N={N} Q={Q} k={k}", flush=True)
+    idx, score, count, _ = rv.retrieve_chunks(bank, query, chunk, **kw)
+    at = torch.tensor([0, 1, 4095, 1 << 20, (1 << 22) - 1, 1 << 22, Q - 1], device="cuda")
+    want_i, want_s, want_c = ORT.retrieve(host(bank), host(query[at]), host(chunk[at]), 20.0, 0.5, 0.02, 1.0, 3, 1, k)
+    assert want_c.max() > 0
+    assert np.array_equal(host(idx[at]), want_i) and np.array_equal(host(count[at]), want_c)
+    assert np.array_equal(host(score[at]), want_s.astype(np.float32))
