@@ -187,8 +187,9 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_f32_kernel(AttentionArgs 
     // items head-major, each XCD a contiguous range: one head's keys and values meet in one L2
     const int n_qt = (a.Lq + 31) / 32;
     const unsigned n_items = (unsigned)n_qt * (unsigned)(a.H * a.layers);
-    const unsigned item = xcd_item(blockIdx.x, n_items);
-    if (item >= n_items) return;  // grid padding (uniform, before any barrier)
+    const unsigned block = row_block();
+    const unsigned item = xcd_item(block, n_items);
+    if (block >= xcd_grid(n_items) || item >= n_items) return;  // grid padding (uniform, before any barrier)
     const int lh = (int)(item / (unsigned)n_qt);  // layer and head
     const int layer = lh / a.H;
     const int hd = lh - layer * a.H;
@@ -1266,7 +1267,7 @@ hipError_t launch_attention_f32(const AttentionArgs& a, hipStream_t stream) {
     if (a.Lq == 0) return hipSuccess;
     const BiasGeom g = make_geom(a);
     const bool bias_on = a.S > 0 && a.lambda != 0.0f;
-    const dim3 grid(xcd_grid((unsigned)((a.Lq + 31) / 32) * (unsigned)(a.H * a.layers))), block(64 * kF32Waves);
+    const dim3 grid = grid_rows(xcd_grid((unsigned)((a.Lq + 31) / 32) * (unsigned)(a.H * a.layers))), block(64 * kF32Waves);
     const float c = a.softmax_scale * kLog2e;
     if (a.D == 64) {
         hipLaunchKernelGGL(attn_f32_kernel<64>, grid, block, 0, stream, a, g, c, bias_on);

@@ -21,6 +21,17 @@ __device__ inline unsigned xcd_item(unsigned block, unsigned n_items) {
     return (block % kXcds) * per_xcd + block / kXcds;
 }
 
+// A launch of one dimension holds fewer than 2^32 threads; the runtime takes a
+// larger count modulo 2^32. A kernel of up to 1023 threads per block whose
+// launches may be larger takes grid_rows(blocks), rows of kGridRow blocks (a
+// multiple of kXcds, so the blocks reach the XCDs in the order of one row), and
+// reads its block from row_block(); past the last one it may be >= blocks.
+constexpr unsigned kGridRow = 1u << 22;
+inline dim3 grid_rows(unsigned blocks) {
+    return blocks <= kGridRow ? dim3(blocks) : dim3(kGridRow, (blocks + kGridRow - 1) / kGridRow);
+}
+__device__ inline unsigned row_block() { return blockIdx.y * kGridRow + blockIdx.x; }
+
 // The streaming driver's layout tables of chunk n, from its retrieval result:
 // the ring slot of every part (in layout order), the KV frame slot table
 // (retrieved frames 0..F-1 when a chunk was retrieved, -1 elsewhere) and the

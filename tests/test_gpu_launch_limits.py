@@ -8,7 +8,7 @@ import torch
 
 import paper_2607_21848_amd as rv
 from oracle import retrieval as ORT
-from tests.gpu_helpers import host
+from tests.gpu_helpers import dev, host
 
 pytestmark = pytest.mark.gpu
 
@@ -44,3 +44,17 @@ def test_retrieval_of_many_queries(k):
     assert want_c.max() > 0
     assert np.array_equal(host(idx[at]), want_i) and np.array_equal(host(count[at]), want_c)
     assert np.array_equal(host(score[at]), want_s.astype(np.float32))
+
+
+def test_fp32_attention_of_many_items():
+    """2^23 + 1 tiles of 32 queries (one key: every output is that key's value). 137 GB."""
+    D, H = 64, 33
+    Lq = 32 * ((1 << 23) // H + 1)
+    q = torch.ones(Lq, H, D, device="cuda")
+    k, v = torch.ones(1, H, D, device="cuda"), torch.randn(1, H, D, device="cuda")
+    print(f"Lq={Lq} H={H} D={D}: {Lq // 32 * H} items", flush=True)
+    o, lse = rv.biased_chunk_attention(q, k, v, dev(np.full(1, -1, np.int32)), None, None, h=1, w=1,
+                                       softmax_scale=D ** -0.5, lam=1.0, sigma=2.0)
+    for c in o.split(1 << 20):
+        assert torch.equal(c, v.expand_as(c))
+    assert (lse - D ** 0.5).abs().max().item() <= 1e-5
