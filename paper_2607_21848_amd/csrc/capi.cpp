@@ -417,9 +417,9 @@ int attention_layers_workspace(const char* fn, int32_t dtype, int32_t Lq, int32_
 }
 
 int32_t attention_max_layers(int32_t Lq, int32_t H, int32_t layers) {
-    // 32-query items (fp32) or 128-query items in at most 16 parts (bf16)
+    // 32-query items (fp32) or 128-query items in at most 16 parts (bf16, 256 threads each)
     const int64_t per_layer = (((int64_t)Lq + 31) / 32 + 16 * (((int64_t)Lq + 127) / 128)) * H;
-    const int64_t most = ((int64_t)1 << 30) / (per_layer > 0 ? per_layer : 1);
+    const int64_t most = (((int64_t)1 << 24) - kXcds) / (per_layer > 0 ? per_layer : 1);
     return most < 1 ? 1 : (int32_t)(most < layers ? most : layers);
 }
 

@@ -160,7 +160,7 @@ int attention_layers(const char* fn, const void* q, const void* k, const void* v
                      size_t workspace_bytes, hipStream_t stream);
 int attention_layers_workspace(const char* fn, int32_t dtype, int32_t Lq, int32_t Lk, int32_t H, int32_t D,
                                int32_t layers, size_t* bytes);
-// Layers that one launch takes at most (a 32-bit count of workgroups).
+// Layers that one launch takes at most (fewer than 2^32 threads).
 int32_t attention_max_layers(int32_t Lq, int32_t H, int32_t layers);
 
 // Scratch of biased_chunk_attention_noalloc: a file-scope device array in

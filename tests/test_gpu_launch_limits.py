@@ -2,6 +2,8 @@
 
 from __future__ import annotations
 
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -58,3 +60,26 @@ def test_fp32_attention_of_many_items():
     for c in o.split(1 << 20):
         assert torch.equal(c, v.expand_as(c))
     assert (lse - D ** 0.5).abs().max().item() <= 1e-5
+
+
+def test_stream_of_many_heads_and_layers():
+    """bf16, one token a chunk, 256 heads of 65536 layers: 2^24 attention items a step. 104 GB."""
+    L, H, D = 1 << 16, 256, 128
+    s = rv.StreamDriver(F=1, h=1, w=1, p=1, H=H, D=D, layers=L, dtype=torch.bfloat16, capacity=5, max_chunks=4, E=4.0,
+                        w_v=0.5, tau_c=0.1, tau_v=0.7, delta=3, eps=0.05, lam=1.0, sigma=2.0, softmax_scale=D ** -0.5,
+                        rope_t_pairs=22, rope_theta=10000.0)
+    depth, K = torch.ones(1, 1, 1, device="cuda"), torch.ones(1, 4, device="cuda")
+    pose = torch.eye(4, device="cuda")[None].contiguous()
+    q = torch.zeros(L, 1, H, D, dtype=torch.bfloat16, device="cuda")
+    vs = []
+    for n in range(2):
+        v = torch.randn(L, 1, H, D, device="cuda", dtype=torch.bfloat16)
+        vs.append(v)
+        print(f"chunk {n}: {L * H} items", flush=True)
+        o, lse = s.step(depth, pose, K, q, q, v)
+        # q = 0: the mean of the values so far, rounded to bf16
+        for l0 in range(0, L, 4096):
+            want = torch.stack([x[l0:l0 + 4096].float() for x in vs]).mean(0)
+            assert (o[l0:l0 + 4096].float() - want).abs().max().item() <= 2.0 ** -7 * max(1.0, want.abs().max().item())
+        assert (lse - math.log(n + 1)).abs().max().item() <= 1e-5
+    s.close()
