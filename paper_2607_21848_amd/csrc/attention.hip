@@ -325,7 +325,8 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_f32_kernel(AttentionArgs 
 #pragma unroll
     for (int w = 0; w < kF32Waves; ++w) {
         const float mw = lds_m[w][n];
-        l_tot += mw == -INFINITY ? 0.0f : lds_l[w][n] * __builtin_amdgcn_exp2f(mw - M);
+        // a wave without a finite logit: a sum of 0, or the NaN of its logits, which has to show
+        l_tot += lds_l[w][n] * (mw == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mw - M));
     }
 #pragma unroll
     for (int half = kF32Waves / 2; half >= 1; half /= 2) {
@@ -354,7 +355,8 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_f32_kernel(AttentionArgs 
             for (int db = 0; db < kDb; ++db) o[db] = O[db][i] * inv;
             *reinterpret_cast<vvec*>(Og + kDb * acc_row(hh, i)) = o;
         }
-        if (a.lse && hh == 0) a.lse[(size_t)lh * a.Lq + q] = (M + log2f(l_tot)) * kLn2;
+        // a row without any weight has no output and no LSE
+        if (a.lse && hh == 0) a.lse[(size_t)lh * a.Lq + q] = l_tot > 0.0f ? (M + log2f(l_tot)) * kLn2 : NAN;
     }
 }
 

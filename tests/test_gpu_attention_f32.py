@@ -77,3 +77,26 @@ def test_no_finite_logit():
                                        softmax_scale=D ** -0.5, lam=1.0, sigma=2.0)
     o, lse = host(o), host(lse)
     assert np.isnan(o[2]).all() and np.isfinite(o[[0, 1, 3]]).all() and np.isfinite(lse[:, [0, 1, 3]]).all()
+    assert np.isnan(lse[:, 2]).all()
+
+
+@pytest.mark.parametrize("where", ["query", "tiles of one wave", "one key"])
+def test_a_nan_shows_in_the_lse(where):
+    """A NaN logit makes its rows' sums NaN, and so their LSE, whichever waves hold it."""
+    Lq, frames, h, w, H, D = 35, 2, 16, 16, 2, 64  # 16 key tiles: two per wave
+    q, k, v, slot, uv, idx = _inputs(13, Lq, frames, h, w, 0, H, D)
+    bad = np.ones(Lq, bool)
+    if where == "query":
+        bad[:] = False
+        bad[[3, 33]] = True
+        q[bad, 0, 5] = np.nan
+    elif where == "tiles of one wave":
+        k[np.r_[96:128, 352:384], 0, 5] = np.nan
+    else:
+        k[100, 0, 5] = np.nan
+    o, lse = rv.biased_chunk_attention(dev(q), dev(k), dev(v), dev(slot), None, None, h=h, w=w,
+                                       softmax_scale=D ** -0.5, lam=1.0, sigma=2.0)
+    o, lse = host(o), host(lse)
+    assert np.isnan(o[bad, 0]).all() and np.isnan(lse[0, bad]).all()
+    assert np.isfinite(o[~bad, 0]).all() and np.isfinite(lse[0, ~bad]).all()
+    assert np.isfinite(o[:, 1]).all() and np.isfinite(lse[1]).all()
