@@ -34,6 +34,7 @@
 // therefore pays one MFMA per biased 32x32 block next to the eight of the
 // QK^T product.
 
+#include <float.h>
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -914,7 +915,9 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttentionArgs a, Bias
     floatx16 O[4];
 #pragma unroll
     for (int db = 0; db < 4; ++db) O[db] = floatx16{0};
-    float m_run = -INFINITY, l_run0 = 0.0f, l_run1 = 0.0f;
+    // a finite start: a tile whose logits are all -inf (the first of a part may be one) then has
+    // weight 0, where -inf - -inf would make the row NaN
+    float m_run = -FLT_MAX, l_run0 = 0.0f, l_run1 = 0.0f;
     // a raw logit above this calls for a rescale: (m_run + kRescaleSlack) / c_log2,
     // so the check needs neither the row's other half nor the scale
     float m_thr = -INFINITY;
@@ -1229,7 +1232,8 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttentionArgs a, Bias
                     *reinterpret_cast<uint2*>(Og + d) = make_uint2(w0, w1);
                 }
             }
-            if (a.lse && hh == 0) a.lse[(size_t)lh * a.Lq + q] = (m_run + log2f(l_tot)) * kLn2;
+            // a row without any weight has no output and no LSE
+            if (a.lse && hh == 0) a.lse[(size_t)lh * a.Lq + q] = l_tot > 0.0f ? (m_run + log2f(l_tot)) * kLn2 : NAN;
         }
     } else {
         // one part of the key range: unnormalised O with its running max and
@@ -1370,7 +1374,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttentionArgs a, KeySpl
     const float inv = 1.0f / L;
     uint16_t* Og = static_cast<uint16_t*>(a.o) + (((size_t)layer * a.q_rows + q) * a.H + (lh - layer * a.H)) * kD + d;
     *reinterpret_cast<uint2*>(Og) = make_uint2(cvt_pk_bf16(acc.x * inv, acc.y * inv), cvt_pk_bf16(acc.z * inv, acc.w * inv));
-    if (a.lse && d == 0) a.lse[(size_t)lh * a.Lq + q] = (M + log2f(L)) * kLn2;
+    if (a.lse && d == 0) a.lse[(size_t)lh * a.Lq + q] = L > 0.0f ? (M + log2f(L)) * kLn2 : NAN;
 }
 
 }  // namespace

@@ -61,3 +61,43 @@ def test_automatic_split_in_a_smaller_workspace():
     with pytest.raises(rv.RevisitError):
         rv.biased_chunk_attention(*long, dev(np.full(1, -1, np.int32)), None, None, h=96, w=88, softmax_scale=0.1, lam=1.0,
                                   sigma=1.0, workspace=torch.empty(16, dtype=torch.uint8, device="cuda"))
+
+
+@pytest.mark.parametrize("parts", [0, 1, 3, 9])
+def test_a_part_that_starts_without_a_finite_logit(parts):
+    """Keys whose logits are -inf have weight 0 in whichever tile they stand, the first of a part
+    (here of every part but the first, and the whole last part) among them, and NaN stays NaN."""
+    Lq, frames, h, w, H = 140, 6, 16, 18, 2  # 54 key tiles
+    q, k, v, slot, uv, idx = _case(Lq, frames, h, w, 2, H, 21)
+    k[:40] /= 4.0
+    q[:, :, 0] = 1.0
+    q[7, 1, 0] = np.nan
+    n = frames * h * w // 32
+    dead = np.concatenate([np.arange(32 * (p * n // P), 32 * (p * n // P) + 32) for P in (2, 3, 4, 8, 9, 16) for p in range(1, P)]
+                          + [np.arange(32 * (8 * n // 9), 32 * n)])
+    k[dead, :, 0] = -np.inf
+    args = [dev(x, torch.bfloat16) for x in (q, k, v)] + [dev(slot), dev(uv), dev(idx)]
+    o, lse = rv.biased_chunk_attention(*args, h=h, w=w, softmax_scale=128 ** -0.5, lam=1.0, sigma=2.0, key_parts=parts)
+    o, lse = host(o), host(lse)
+    assert np.isnan(o[7, 1]).all() and np.isnan(lse[1, 7])
+    q[7, 1, 0] = 1.0
+    k[dead] = 0.0
+    k[dead, :, 0] = -2.0 ** 100  # the same weights, in finite numbers
+    Oo, Lo = OA.biased_attention(q, k, v, slot, uv, idx, h, w, 128 ** -0.5, 1.0, 2.0)
+    rest = np.ones((Lq, H), bool)
+    rest[7, 1] = False
+    assert np.abs(o - Oo)[rest].max() <= 2e-2 and np.abs(lse - Lo).T[rest].max() <= 4e-3
+
+
+@pytest.mark.parametrize("parts", [0, 1, 5])
+def test_a_row_without_a_finite_logit(parts):
+    """Such a row has no weights: its output and its LSE are not numbers, its neighbours' are."""
+    q, k, v, slot, uv, idx = _case(60, 5, 9, 16, 2, 2, 22)
+    q[:, :, 0] = k[:, :, 0] = 1.0
+    q[9, 1, 0] = -np.inf
+    args = [dev(x, torch.bfloat16) for x in (q, k, v)] + [dev(slot), dev(uv), dev(idx)]
+    o, lse = rv.biased_chunk_attention(*args, h=9, w=16, softmax_scale=128 ** -0.5, lam=1.0, sigma=2.0, key_parts=parts)
+    o, lse = host(o), host(lse)
+    rest = np.ones((60, 2), bool)
+    rest[9, 1] = False
+    assert np.isnan(o[9, 1]).all() and np.isnan(lse[1, 9]) and np.isfinite(o[rest]).all() and np.isfinite(lse.T[rest]).all()
