@@ -263,9 +263,13 @@ int reproject_correspondence(const float* tgt_depth, const float* tgt_c2w, const
  *               shape and key_parts on the same device (items * P * 66.5 KiB
  *               when P > 1, else 0), 16-byte aligned; may be NULL / 0 when
  *               that size is 0. Too small: REVISIT_ERR_SHAPE; NULL while
- *               needed: REVISIT_ERR_NULL. With key_parts = 0 and fewer than 256
- *               key tiles of 32 keys a smaller one, or none, is taken too: the
- *               keys are then cut into as many parts as fit in it.
+ *               needed: REVISIT_ERR_NULL. With key_parts = 0 a smaller one, or
+ *               none, is taken too where the call can do without: with fewer
+ *               than 256 key tiles of 32 keys, and where the items alone fill
+ *               two workgroups per compute unit to 97 % in their last round,
+ *               or make four such rounds and no 2 to 4 parts of 128 tiles or
+ *               more do. The keys are then cut into as many parts as fit in it
+ *               (one that is not 16-byte aligned counts as none).
  */
 int biased_chunk_attention(const void* q, const void* k, const void* v, void* o,
                            float* lse, int32_t dtype,
@@ -294,15 +298,17 @@ int rc_attention_workspace_size(int32_t dtype, int32_t Lq, int32_t Lk, int32_t H
  * partial results in a library array of 128 MiB per device (a static device
  * array: each device the library runs on holds its own copy until the
  * process ends).
- *   key_parts = 0  the automatic split, cut to the most parts whose partial
- *                  results fit in 128 MiB (items * P * 66.5 KiB); the results
- *                  then equal biased_chunk_attention's with that P;
+ *   key_parts = 0  where biased_chunk_attention does without a workspace (see
+ *                  there), one part, so that the call leaves the array alone;
+ *                  else the automatic split, cut to the most parts whose
+ *                  partial results fit in 128 MiB (items * P * 66.5 KiB). The
+ *                  results equal biased_chunk_attention's with that P;
  *   key_parts > 0  as for biased_chunk_attention; REVISIT_ERR_SHAPE when its
  *                  partial results need more than 128 MiB.
- * Every call on one device shares that device's array, which keeps the last
- * call's contents: calls that may overlap in time on one device (different
- * streams, graph replays beside other calls) race, and the caller must
- * order them. Nothing in it needs to start at zero: every partial result the
+ * Every split call on one device shares that device's array, which keeps the
+ * last one's contents: split calls that may overlap in time on one device
+ * (different streams, graph replays beside other calls) race, and the caller
+ * must order them. Nothing in it needs to start at zero: every partial result the
  * merge reads is written earlier in the same call. The first call on a
  * device looks the array's address up (REVISIT_ERR_LAUNCH if that fails).
  */

@@ -99,6 +99,15 @@ int attention_parts(const char* fn, const revisit::AttentionArgs& a, int32_t key
     return REVISIT_OK;
 }
 
+// Key parts whose workspace an automatic call has to bring at least (1: none).
+int attention_least_parts(const char* fn, const revisit::AttentionArgs& a, int32_t* parts) {
+    int cus = 0;
+    const hipError_t e = device_compute_units(&cus);
+    if (e != hipSuccess) return fail(REVISIT_ERR_LAUNCH, "%s: device query failed: %s", fn, hipGetErrorString(e));
+    *parts = revisit::attention_bf16_least_parts(a, 2 * cus);
+    return REVISIT_OK;
+}
+
 }  // namespace
 
 namespace revisit {
@@ -367,10 +376,10 @@ int run_attention(const char* fn, const revisit::AttentionArgs& a, int32_t dtype
     if (st != REVISIT_OK) return st;
     const bool usable = workspace && aligned(workspace, kWorkspaceAlign);
     if (need > 0 && key_parts == 0 && (workspace_bytes < need || !usable)) {
-        int cus = 0;
-        const hipError_t e = device_compute_units(&cus);
-        if (e != hipSuccess) return fail(REVISIT_ERR_LAUNCH, "%s: device query failed: %s", fn, hipGetErrorString(e));
-        const size_t least = revisit::attention_bf16_workspace_bytes(a, revisit::attention_bf16_least_parts(a, 2 * cus));
+        int32_t fewest = 1;
+        st = attention_least_parts(fn, a, &fewest);
+        if (st != REVISIT_OK) return st;
+        const size_t least = revisit::attention_bf16_workspace_bytes(a, fewest);
         if (least == 0 || (least <= workspace_bytes && usable)) {
             const size_t have = usable ? workspace_bytes : 0;
             while (parts > 1 && revisit::attention_bf16_workspace_bytes(a, parts) > have) --parts;
@@ -456,6 +465,16 @@ int biased_chunk_attention_noalloc(const void* q, const void* k, const void* v, 
     size_t need = 0;
     st = attention_parts(fn, a, key_parts, &parts, &need);
     if (st != REVISIT_OK) return st;
+    if (need > 0 && key_parts == 0) {
+        // a call that can do without a workspace leaves the shared array alone
+        int32_t least = 1;
+        st = attention_least_parts(fn, a, &least);
+        if (st != REVISIT_OK) return st;
+        if (least == 1) {
+            parts = 1;
+            need = 0;
+        }
+    }
     if (need > revisit::kAttentionScratchBytes) {
         if (key_parts != 0)
             return fail(REVISIT_ERR_SHAPE, "%s: %d key parts need %zu bytes of scratch, more than the %zu bytes it holds "

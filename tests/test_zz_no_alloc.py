@@ -78,3 +78,14 @@ def test_noalloc_refuses_a_split_beyond_its_scratch():
     with pytest.raises(rv.RevisitError) as e:
         rv.biased_chunk_attention(q, k, v, slot, uv, idx, **kw, key_parts=64, noalloc=True)
     assert e.value.status == 2 and "scratch" in str(e.value)
+
+
+@pytest.mark.parametrize("Lq,nf,H,h,w", [(60, 5, 3, 9, 16), (1170, 18, 12, 15, 26)])
+def test_noalloc_leaves_the_scratch_alone_where_a_split_is_not_needed(Lq, nf, H, h, w):
+    """Short key ranges run unsplit, so that such calls on two streams share nothing (the workspace
+    entry point splits these)."""
+    assert rv.attention_workspace_size(torch.bfloat16, Lq, nf * h * w, H, 128) > 0
+    (q, k, v, slot, uv, idx), kw = _case(5, Lq, nf, H, 2, h, w)
+    o_na, lse_na = rv.biased_chunk_attention(q, k, v, slot, uv, idx, **kw, noalloc=True)
+    o_1, lse_1 = rv.biased_chunk_attention(q, k, v, slot, uv, idx, **kw, key_parts=1)
+    assert torch.equal(o_na, o_1) and torch.equal(lse_na, lse_1)
