@@ -79,12 +79,12 @@ struct BiasGeom {
 // fp32 kernel: v_mfma_f32_32x32x2_f32 (64 cycles each), so a 32-query,
 // 32-key tile keeps a SIMD's matrix core busy for 8192 cycles at D = 128
 // while it needs 32 KB of keys and values: bound by the matrix cores as long
-// as nothing waits. One workgroup takes 32 queries of one head; its kF32Waves
-// waves take every kF32Waves-th key tile each and work without a barrier
+// as nothing waits. One workgroup takes 32 queries of one head; its kWaves
+// waves (f32_waves) take every kWaves-th key tile each and work without a barrier
 // until they merge their results through LDS. That split leaves the chip's
 // last round of workgroups small (12 heads of 4680 queries are 1764 items,
 // 6.9 per compute unit, where 128-query items fill 444 of 512 places), and
-// gives a small problem eight waves per 32 queries.
+// gives a small problem several waves per 32 queries.
 //
 // Operands come straight from global memory into registers, 16 bytes a lane.
 // The contraction index of an MFMA may be any numbering that both operands
@@ -103,9 +103,8 @@ struct BiasGeom {
 // kernel before it (128 queries per workgroup, tiles staged through registers
 // into LDS between two barriers, one 4-byte LDS read per MFMA) took 24.5 ms.
 // Four waves per item, two workgroups per compute unit: 7.48 ms. Lq 64, Lk 256,
-// D 64, one head: 8 us where the eight tiles took 54 us one after the other.
+// D 64, one head without bias: 8.6 us in four waves (36 before, 9.3 in eight).
 // ---------------------------------------------------------------------------
-constexpr int kF32Waves = 8;
 
 // The correspondence of a lane's query in KV frame f.
 struct F32Corr {
@@ -170,15 +169,15 @@ __device__ __forceinline__ void f32_bias(floatx16& acc, F32Corr& c, const Attent
     }
 }
 
-template <int D>
-__global__ __launch_bounds__(64 * kF32Waves) void attn_f32_kernel(AttentionArgs a, BiasGeom g, float c_log2,
+template <int D, int kWaves>
+__global__ __launch_bounds__(64 * kWaves, 2) void attn_f32_kernel(AttentionArgs a, BiasGeom g, float c_log2,
                                                                   bool bias_on) {
     constexpr int TK = 32;
     constexpr int kG = D / 8;    // key vectors of a lane and tile
     constexpr int kDb = D / 32;  // 32-dim blocks of the output
     typedef float vvec __attribute__((ext_vector_type(kDb)));
-    __shared__ float lds_o[kF32Waves / 2][kDb * 16 * 64];
-    __shared__ float lds_m[kF32Waves][32], lds_l[kF32Waves][32];
+    __shared__ float lds_o[kWaves > 1 ? kWaves / 2 : 1][kWaves > 1 ? kDb * 16 * 64 : 1];
+    __shared__ float lds_m[kWaves][32], lds_l[kWaves][32];
     __shared__ floatx4 lds_q[kG][64];  // the query vector of each lane, per four QK steps
 
     const int lane = threadIdx.x & 63;
@@ -203,7 +202,7 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_f32_kernel(AttentionArgs 
     const uint8_t* Kg = static_cast<const uint8_t*>(a.k) + kv_byte0;
     const uint8_t* Vg = static_cast<const uint8_t*>(a.v) + kv_byte0;
 
-    for (int j = wave; j < kG; j += kF32Waves) {
+    for (int j = wave; j < kG; j += kWaves) {
         const float* Qg = static_cast<const float*>(a.q) + ((q_row0 + q) * a.H + hd) * D + 4 * hh;
         lds_q[j][lane] = q_ok ? *reinterpret_cast<const floatx4*>(Qg + 8 * j) : floatx4{0, 0, 0, 0};
     }
@@ -302,49 +301,51 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_f32_kernel(AttentionArgs 
 #pragma unroll
         for (int j = 0; j < kG; ++j) load_k(kb, ko, j);
         int t = wave;
-        for (; (t + 1) * TK <= Lk; t += kF32Waves) {
-            tile(std::true_type{}, t * TK, min(t + kF32Waves, n_tiles - 1) * TK);
+        for (; (t + 1) * TK <= Lk; t += kWaves) {
+            tile(std::true_type{}, t * TK, min(t + kWaves, n_tiles - 1) * TK);
         }
         if (t < n_tiles) tile(std::false_type{}, t * TK, t * TK);
     }
 
-    // merge: every wave scales its sums to the rows' common maximum, then the
-    // upper half of the remaining waves hands its sums to the lower half
-    float l_tot = half_swap_sum(l_run);
-    if (hh == 0) {
-        lds_m[wave][n] = m_run;
-        lds_l[wave][n] = l_tot;
-    }
-    __syncthreads();
-    float M = -INFINITY;
-#pragma unroll
-    for (int w = 0; w < kF32Waves; ++w) M = fmaxf(M, lds_m[w][n]);
-    const float mine = m_run == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m_run - M);
-#pragma unroll
-    for (int db = 0; db < kDb; ++db) O[db] *= mine;
-    l_tot = 0.0f;
-#pragma unroll
-    for (int w = 0; w < kF32Waves; ++w) {
-        const float mw = lds_m[w][n];
-        // a wave without a finite logit: a sum of 0, or the NaN of its logits, which has to show
-        l_tot += lds_l[w][n] * (mw == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mw - M));
-    }
-#pragma unroll
-    for (int half = kF32Waves / 2; half >= 1; half /= 2) {
-        if (wave >= half && wave < 2 * half) {
-#pragma unroll
-            for (int db = 0; db < kDb; ++db)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) lds_o[wave - half][(db * 16 + i) * 64 + lane] = O[db][i];
+    float l_tot = half_swap_sum(l_run), M = m_run;
+    if constexpr (kWaves > 1) {
+        // merge: every wave scales its sums to the rows' common maximum, then the
+        // upper half of the remaining waves hands its sums to the lower half
+        if (hh == 0) {
+            lds_m[wave][n] = m_run;
+            lds_l[wave][n] = l_tot;
         }
         __syncthreads();
-        if (wave < half) {
+        M = -INFINITY;
 #pragma unroll
-            for (int db = 0; db < kDb; ++db)
+        for (int w = 0; w < kWaves; ++w) M = fmaxf(M, lds_m[w][n]);
+        const float mine = m_run == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m_run - M);
 #pragma unroll
-                for (int i = 0; i < 16; ++i) O[db][i] += lds_o[wave][(db * 16 + i) * 64 + lane];
+        for (int db = 0; db < kDb; ++db) O[db] *= mine;
+        l_tot = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            const float mw = lds_m[w][n];
+            // a wave without a finite logit: a sum of 0, or the NaN of its logits, which has to show
+            l_tot += lds_l[w][n] * (mw == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mw - M));
         }
-        __syncthreads();
+#pragma unroll
+        for (int half = kWaves / 2; half >= 1; half /= 2) {
+            if (wave >= half && wave < 2 * half) {
+#pragma unroll
+                for (int db = 0; db < kDb; ++db)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) lds_o[wave - half][(db * 16 + i) * 64 + lane] = O[db][i];
+            }
+            __syncthreads();
+            if (wave < half) {
+#pragma unroll
+                for (int db = 0; db < kDb; ++db)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) O[db][i] += lds_o[wave][(db * 16 + i) * 64 + lane];
+            }
+            __syncthreads();
+        }
     }
     if (wave == 0 && q_ok) {
         const float inv = 1.0f / l_tot;
@@ -1269,17 +1270,38 @@ BiasGeom make_geom(const AttentionArgs& a) {
 
 }  // namespace
 
+// Waves per item of the fp32 kernel. Eight for long key ranges (at 128 tiles four
+// are 1 to 17% slower: more items per workgroup place fill the last round worse);
+// four where the merge of eight, 64 KB through LDS and one workgroup per compute
+// unit, weighs more than that (12 tiles, 7500 items of D 128: 469 against 586 us,
+// 995 in the kernel before); one, which merges nothing, for short ranges of items
+// that fill the chip by themselves (one tile of one key, 7500 items: 89 us, 152 in four
+// waves, 295 in eight, 128 before; two tiles, 1764 items: 33, 47, 74 and 61). Items
+// that do not fill it last as long as a wave's turns: from two tiles on they take four.
+static int f32_waves(unsigned items, int n_tiles) {
+    if (n_tiles >= 48) return 8;
+    return n_tiles >= 12 || (n_tiles >= 2 && items <= 512) ? 4 : 1;
+}
+
 hipError_t launch_attention_f32(const AttentionArgs& a, hipStream_t stream) {
     if (a.Lq == 0) return hipSuccess;
     const BiasGeom g = make_geom(a);
     const bool bias_on = a.S > 0 && a.lambda != 0.0f;
-    const dim3 grid = grid_rows(xcd_grid((unsigned)((a.Lq + 31) / 32) * (unsigned)(a.H * a.layers))), block(64 * kF32Waves);
+    const unsigned items = (unsigned)((a.Lq + 31) / 32) * (unsigned)(a.H * a.layers);
+    const dim3 grid = grid_rows(xcd_grid(items));
     const float c = a.softmax_scale * kLog2e;
-    if (a.D == 64) {
-        hipLaunchKernelGGL(attn_f32_kernel<64>, grid, block, 0, stream, a, g, c, bias_on);
-    } else {
-        hipLaunchKernelGGL(attn_f32_kernel<128>, grid, block, 0, stream, a, g, c, bias_on);
-    }
+    const int waves = f32_waves(items, (a.Lk + 31) / 32);
+    auto launch = [&](auto d_tag, auto waves_tag) {
+        constexpr int D = decltype(d_tag)::value, W = decltype(waves_tag)::value;
+        hipLaunchKernelGGL((attn_f32_kernel<D, W>), grid, dim3(64 * W), 0, stream, a, g, c, bias_on);
+    };
+    auto launch_d = [&](auto d_tag) {
+        if (waves == 8) launch(d_tag, std::integral_constant<int, 8>{});
+        else if (waves == 4) launch(d_tag, std::integral_constant<int, 4>{});
+        else launch(d_tag, std::integral_constant<int, 1>{});
+    };
+    if (a.D == 64) launch_d(std::integral_constant<int, 64>{});
+    else launch_d(std::integral_constant<int, 128>{});
     return hipGetLastError();
 }
 
