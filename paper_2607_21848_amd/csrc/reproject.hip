@@ -44,10 +44,14 @@ namespace {
 constexpr int kBlock = 128;  // measured 1-2% faster than 256 (and than 64, 512, 1024)
 constexpr int kMaxSrcLds = 64;  // source frames per problem
 constexpr int64_t kSmallLaunch = 512;  // token blocks below which a block takes one source
-// A large rotation launch of few sources: fewer sources than this, at least so
-// many tokens a frame and (token, source) pairs in all (100 MB of results); and
-// the blocks that rotation_source_kernel's launches should have.
+// A large rotation launch of few sources: fewer sources than kRotationSources, at
+// least so many tokens a frame and (token, source) pairs in all (100 MB of
+// results); where every frame ends on a line, fewer than kLineSources, or one
+// more for frames of middle size. And the blocks that rotation_source_kernel's
+// launches should have.
 constexpr int kRotationSources = 8;
+constexpr int kLineSources = 3, kLineMinTokens = 768, kLineMaxTokens = 8192;
+constexpr int kLineTokens = 16;  // tokens whose u^ fill a 128-byte line
 constexpr int kRotationTokens = 512;
 constexpr int64_t kRotationPairs = 9000000;
 constexpr int64_t kRotationBlocks = 2048;
@@ -571,12 +575,16 @@ __device__ __forceinline__ void rotate_pair(const ReprojectArgs& a, const double
 // the block writes one contiguous range with plain stores. Taken where the
 // launch above would have too few blocks (16 problems of 30 x 52 tokens and 6
 // sources: 8.3 -> 5.9 us; of 8 x 12 and 12: 9.6 -> 4.3), and for large
-// launches of few sources, whose blocks above spend a long time on S
-// homographies for S writes and end lines in the middle: 1024 problems of 30 x 52
-// and 6 sources 89 -> 78 us (345 MB, 4.4 TB/s; stores alone reach 5.2 in this
-// order and 4.3 in the other). Between those, and from 8 sources on, the
-// kernel above is the faster (200 problems: 19.4 against 21.1 us; 512 problems of 45 x 80
-// and 12 sources: 154 against 164).
+// launches of few sources whose frames end in the middle of a line: the launch
+// above writes past the L2, one source after the other, and a line cut
+// between two frames costs it twice (1024 problems of 30 x 52 and 6 sources
+// 89 -> 78 us, 345 MB; 45 x 79 and 6 sources, 33 million pairs, 1.64 times as
+// fast). Where frames end on lines it is the faster one (the same pairs of
+// 45 x 80: 1.07 times, of 128 x 128: 1.35 times) but for one or two sources, whose
+// homographies its blocks wait for (1.22 to 1.8 times), and three (1.03 to 1.16
+// times between 768 and 8192 tokens, 0.85 to 0.97 outside). Between small and
+// large, and from 8 sources on, the kernel above is kept (200 problems: 19.4
+// against 21.1 us; 512 problems of 45 x 80 and 12 sources: 154 against 164).
 struct RotationSplit {
     int32_t chunk, chunks;
 };
@@ -703,7 +711,9 @@ hipError_t launch_rotation(const ReprojectArgs& a, hipStream_t stream) {
     if (blocks > INT32_MAX - kXcds) return hipErrorInvalidValue;
     const dim3 block(kBlock);
     const int64_t frames = (int64_t)a.B * a.S * a.Tq;  // (problem, source, target frame)
-    const bool large = a.S < kRotationSources && hw >= kRotationTokens && frames * hw >= kRotationPairs;
+    const int few = hw % kLineTokens != 0 ? kRotationSources
+                                          : kLineSources + (hw >= kLineMinTokens && hw <= kLineMaxTokens ? 1 : 0);
+    const bool large = a.S < few && hw >= kRotationTokens && frames * hw >= kRotationPairs;
     const int64_t max_chunks = (hw / 2 + kBlock) / kBlock;  // blocks of one pair per thread
     if ((blocks < kSmallLaunch || large) && frames * max_chunks <= INT32_MAX / 2) {
         const int64_t want = (kRotationBlocks + frames - 1) / frames;

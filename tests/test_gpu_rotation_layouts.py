@@ -27,10 +27,12 @@ def _bits(t):
 # (B, Tq, S, h, w): more than 512 blocks of all sources, little output; the same with odd frames;
 # frames of one partial block; 9.1e6 pairs and few sources (a block per source), odd and even; one
 # column of odd height whose blocks take more than 128 pairs, in a small and in a large launch (the
-# column of a thread's token is then stepped by 0)
+# column of a thread's token is then stepped by 0); frames that end on lines, of three sources (a
+# block per source) and of four
 @pytest.mark.parametrize("B,Tq,S,h,w", [(60, 3, 6, 30, 52), (40, 3, 9, 45, 35), (600, 1, 3, 5, 7), (650, 3, 3, 30, 52),
                                         (600, 1, 7, 41, 53), (520, 1, 1, 1, 1), (10, 4, 64, 301, 1),
-                                        (2600, 1, 7, 513, 1)])
+                                        (2600, 1, 7, 513, 1), (2700, 1, 3, 30, 40),
+                                        (2000, 1, 4, 30, 40)])
 @pytest.mark.parametrize("shift", [0, 1])
 def test_launches_agree(B, Tq, S, h, w, shift):
     tc, tk, sc, sk = W.make_rotation_batch(B, Tq=Tq, S=S, h=h, w=w, p=2, distinct=5, seed=B + h)
