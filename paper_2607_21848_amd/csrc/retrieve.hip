@@ -429,11 +429,15 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void retrieve_merge_kernel(Retri
     finish(a, sh, qi, count);
 }
 
-// Waves of a workgroup over n entries, `each` per wave, as many as a launch of
-// n_query workgroups has threads for: fewer than 2^32 (the runtime takes a larger
-// count modulo 2^32).
+// Waves of a workgroup over n entries, `each` per wave, as far as n_query
+// workgroups do not fill the chip by themselves: past that the meeting of a
+// query's waves only costs (3000 entries, 4096 queries, k 1: 67 us in twelve waves
+// each, 39 in one; k 32 with every entry in reach 689 against 70; at 1024
+// queries 20 in twelve, 14 in four). One wave each is also what the largest
+// launches hold, 2^32 threads (the runtime takes a larger count modulo 2^32).
+constexpr int kFillWaves = 4096;
 dim3 waves_for(int64_t n, int each, int32_t n_query) {
-    const int64_t most = (((int64_t)1 << 32) - 1) / kWave / n_query;
+    const int64_t most = kFillWaves / n_query;
     int64_t w = (n + each - 1) / each;
     w = w < kMaxWaves ? w : kMaxWaves;
     w = w < most ? w : most;
