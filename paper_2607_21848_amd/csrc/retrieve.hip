@@ -52,10 +52,12 @@ constexpr int kLane = 4;                               // best pairs a lane keep
 constexpr int kMaxK = 32;
 constexpr int kRankLanes = 8;                          // lanes that count one pair's rank
 // Pairs are ranked by counting without a reduction first when that takes each
-// thread at most kRankCost comparisons per result wanted (16 comparisons take
-// about as long as one result's round of the waves' reductions, 18 dependent
-// lane exchanges).
-constexpr int kRankCost = 16;
+// thread at most so many comparisons per result wanted (and one more): as long as
+// one result's round of the waves' reductions, 18 dependent lane exchanges, which get
+// in each other's way when there are many waves. Measured equal at 2.5 to 4 in one
+// wave (37 of 48 pairs, k 8: 7.1 us counted, 7.6 reduced; 45: 8.2 and 7.7), at 5 to 7 in
+// four and eight, at 7 to 10 in sixteen (496 pairs, k 32: 31 and 40; k 16: 30 and 24).
+__device__ __forceinline__ int rank_cost(int n_waves) { return 3 + 5 * (31 - __clz(n_waves)) / 4; }
 
 // (s1, j1) strictly before (s2, j2): smaller score, then smaller index.
 __device__ __forceinline__ bool before(double s1, int j1, double s2, int j2) {
@@ -127,13 +129,16 @@ __device__ __forceinline__ void wave_first(double& s, int& j) {
     }
 }
 
+template <int kWaves>
 struct Shared {
-    double s[kMaxWaves * kMaxK];  // collected pairs, in any order
-    int j[kMaxWaves * kMaxK];
+    // what all waves' results come to, or all that one wave holds
+    static constexpr int kPairs = kWaves > 1 ? kWaves * kMaxK : kLane * kWave;
+    double s[kPairs];  // collected pairs, in any order
+    int j[kPairs];
     double res_s[kMaxK];  // the first pairs of this scan
     int res_j[kMaxK];
-    double drop_s[kMaxWaves];
-    int drop_j[kMaxWaves];
+    double drop_s[kWaves];
+    int drop_j[kWaves];
     int out_j[kMaxK];  // chunk ids of the results so far
     int pairs, kept;
 };
@@ -145,9 +150,9 @@ struct Shared {
 // put(r, s, j) for result r in one thread and returns the number found (the
 // same in every thread). scan is called with offer(s, j), once per pass over
 // the data, by every thread for its share. Every thread of the workgroup
-// (whole waves) calls this together.
-template <bool kMany, class Scan, class Put>
-__device__ __forceinline__ int first_k(Shared& sh, int k, Scan scan, Put put) {
+// (whole waves, at most kWaves) calls this together.
+template <bool kMany, int kWaves, class Scan, class Put>
+__device__ __forceinline__ int first_k(Shared<kWaves>& sh, int k, Scan scan, Put put) {
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int wave = tid / kWave;
@@ -173,6 +178,40 @@ __device__ __forceinline__ int first_k(Shared& sh, int k, Scan scan, Put put) {
             have[i] = __ballot(top.j[i] != INT32_MAX);
             mine += __popcll(have[i]);
         }
+        // the wave's first pairs, one per round of a reduction: lane r gets the r-th
+        auto wave_rounds = [&](int most, double& ws, int& wj) __attribute__((always_inline)) {
+            ws = INFINITY;
+            wj = INT32_MAX;
+            int n = 0;
+            for (; n < most; ++n) {
+                double bs = top.s[0];
+                int bj = top.j[0];
+                wave_first(bs, bj);
+                if (bj == INT32_MAX) break;
+                if (top.j[0] == bj) top.pop();
+                if (lane == n) {
+                    ws = bs;
+                    wj = bj;
+                }
+            }
+            return n;
+        };
+        if constexpr (!kMany && kWaves == 1) {
+            // one wave has its results from the reductions alone, at 0.41 us each; counting ranks
+            // takes 0.06 us a pair, more from some thirty on (200 entries, k 1: 3.2 us, all
+            // of them in reach 3.7; through LDS 3.5 and 4.4)
+            const int found = min(k, mine);
+            if (found == 1 || found * 512 <= mine * (64 + mine)) {
+                double ws;
+                int wj;
+                wave_rounds(found, ws, wj);
+                if (lane < found) {
+                    put(lane, ws, wj);
+                    sh.out_j[lane] = wj;
+                }
+                return found;
+            }
+        }
         int base = 0;
         if (lane == 0) {
             base = mine ? atomicAdd(&sh.pairs, mine) : 0;
@@ -189,7 +228,7 @@ __device__ __forceinline__ int first_k(Shared& sh, int k, Scan scan, Put put) {
         __syncthreads();
         const int need = k - done;
         int m = sh.pairs;
-        if (m <= kMaxWaves * kMaxK && m * m <= (int)blockDim.x * kRankCost * need) {
+        if (m <= Shared<kWaves>::kPairs && m * m <= (int)blockDim.x * rank_cost(n_waves) * (need + 1)) {
 #pragma unroll
             for (int i = 0; i < kLane; ++i) {
                 if (top.j[i] != INT32_MAX) {
@@ -201,20 +240,9 @@ __device__ __forceinline__ int first_k(Shared& sh, int k, Scan scan, Put put) {
             }
             __syncthreads();
         } else {
-            double ws = INFINITY;  // lane r keeps the wave's r-th pair
-            int wj = INT32_MAX;
-            int n = 0;
-            for (; n < need; ++n) {
-                double bs = top.s[0];
-                int bj = top.j[0];
-                wave_first(bs, bj);
-                if (bj == INT32_MAX) break;
-                if (top.j[0] == bj) top.pop();
-                if (lane == n) {
-                    ws = bs;
-                    wj = bj;
-                }
-            }
+            double ws;
+            int wj;
+            const int n = wave_rounds(need, ws, wj);
             int at = 0;
             if (lane == 0 && n) at = atomicAdd(&sh.kept, n);
             at = __shfl(at, 0);
@@ -357,7 +385,8 @@ __device__ __forceinline__ void put_result(const RetrieveArgs& a, int qi, int r,
 }
 
 // What follows the results of query qi: the empty places, the count and the frame selection.
-__device__ __forceinline__ void finish(const RetrieveArgs& a, Shared& sh, int qi, int count) {
+template <int kWaves>
+__device__ __forceinline__ void finish(const RetrieveArgs& a, Shared<kWaves>& sh, int qi, int count) {
     const int tid = threadIdx.x;
     if (tid >= count && tid < a.k) {
         a.out_idx[(size_t)qi * a.k + tid] = -1;
@@ -375,12 +404,12 @@ __device__ __forceinline__ void finish(const RetrieveArgs& a, Shared& sh, int qi
 }
 
 // The whole bank for query blockIdx.x.
-template <bool kMany>
-__global__ __launch_bounds__(kMaxWaves * kWave) void retrieve_kernel(RetrieveArgs a) {
-    __shared__ Shared sh;
+template <bool kMany, int kWaves>
+__global__ __launch_bounds__(kWaves * kWave) void retrieve_kernel(RetrieveArgs a) {
+    __shared__ Shared<kWaves> sh;
     const int qi = blockIdx.x;
     const QueryPose qp = query_pose(a, qi);
-    const int count = first_k<kMany>(
+    const int count = first_k<kMany, kWaves>(
         sh, a.k, [&](auto offer) { scan_bank(a, qp.lo, qp.hi, qp, offer); },
         [&](int r, double s, int j) { put_result(a, qi, r, s, j); });
     finish(a, sh, qi, count);
@@ -392,7 +421,7 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void retrieve_kernel(RetrieveArg
 // to all but the first.
 template <bool kMany>
 __global__ __launch_bounds__(kSegWaves * kWave) void retrieve_segment_kernel(RetrieveArgs a) {
-    __shared__ Shared sh;
+    __shared__ Shared<kSegWaves> sh;
     const unsigned n_items = (unsigned)a.n_seg * (unsigned)a.n_query;
     const unsigned item = xcd_item(blockIdx.x, n_items);
     if (item >= n_items) return;  // grid padding (uniform, before any barrier)
@@ -406,18 +435,18 @@ __global__ __launch_bounds__(kSegWaves * kWave) void retrieve_segment_kernel(Ret
         a.seg_s[base + r] = s;
         a.seg_j[base + r] = j;
     };
-    const int count = first_k<kMany>(sh, a.k, [&](auto offer) { scan_bank(a, begin, end, qp, offer); }, put);
+    const int count = first_k<kMany, kSegWaves>(sh, a.k, [&](auto offer) { scan_bank(a, begin, end, qp, offer); }, put);
     if ((int)threadIdx.x >= count && (int)threadIdx.x < a.k) put(threadIdx.x, INFINITY, INT32_MAX);
 }
 
 // The results of query blockIdx.x from its n_seg * k segment results.
 template <bool kMany>
 __global__ __launch_bounds__(kMaxWaves * kWave) void retrieve_merge_kernel(RetrieveArgs a) {
-    __shared__ Shared sh;
+    __shared__ Shared<kMaxWaves> sh;
     const int qi = blockIdx.x;
     const size_t base = (size_t)qi * a.n_seg * a.k;
     const int n_cand = a.n_seg * a.k;
-    const int count = first_k<kMany>(
+    const int count = first_k<kMany, kMaxWaves>(
         sh, a.k,
         [&](auto offer) {
             for (int c = threadIdx.x; c < n_cand; c += blockDim.x) {
@@ -459,7 +488,9 @@ template <bool kMany>
 static hipError_t launch_many(const RetrieveArgs& a, hipStream_t stream) {
     if (a.n_seg == 0) {
         // one batch of loads per lane where 16 waves suffice for that: 3000 entries took 17 us in one wave, 8.8 us in twelve
-        hipLaunchKernelGGL(retrieve_kernel<kMany>, dim3(a.n_query), waves_for(a.n_bank, kUnroll * kWave, a.n_query), 0, stream, a);
+        const dim3 block = waves_for(a.n_bank, kUnroll * kWave, a.n_query);
+        if (block.x == kWave) hipLaunchKernelGGL((retrieve_kernel<kMany, 1>), dim3(a.n_query), block, 0, stream, a);
+        else hipLaunchKernelGGL((retrieve_kernel<kMany, kMaxWaves>), dim3(a.n_query), block, 0, stream, a);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(retrieve_segment_kernel<kMany>, dim3(xcd_grid((unsigned)a.n_query * a.n_seg)), dim3(kSegWaves * kWave), 0,

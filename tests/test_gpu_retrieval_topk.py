@@ -73,3 +73,31 @@ def test_distances_at_the_gate():
     _check(_line(x), _line(np.zeros(1)), np.array([100], np.int32), 32, E=float(E), tau_c=float(tau))
     _check(_line(np.zeros(70)), _line(np.zeros(1)), np.array([100], np.int32), 32, tau_c=0.0)
     _check(_line(x), _line(np.zeros(1)), np.array([100], np.int32), 4, tau_c=-1.0)
+
+
+@pytest.mark.parametrize("N", [30, 200, 256, 300])
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 8])
+def test_few_and_many_in_reach_of_one_wave(N, k):
+    """Around the sizes from which a wave's results come from reductions alone, and its pairs are not
+    ranked: 0 to 9, some twenty and thirty, and all entries in reach."""
+    rng = np.random.default_rng(N + k)
+    x = rng.permutation(N).astype(np.float32) + 1.0
+    x[::7] = np.ceil(x[::7] / 4) * 4  # equal scores too
+    for reach in (0, 1, 2, 3, 4, 6, 9, 19, 20, 21, 22, 30, 37, 45, 64, 65, 140, N):
+        _check(_line(x), _line(np.zeros(1)), np.array([N + 5], np.int32), k, E=1.0, tau_c=reach + 0.5)
+
+
+@pytest.mark.parametrize("N,Q", [(3000, 300), (3000, 1500), (8192, 2049), (700, 5000)])
+@pytest.mark.parametrize("k", [1, 4, 9, 32])
+def test_many_queries(N, Q, k):
+    """So many queries that each has fewer waves than its bank would fill, or one."""
+    rng = np.random.default_rng(Q + k)
+    bank, query = _line(rng.uniform(0, 9, N)), _line(rng.uniform(0, 9, Q))
+    chunk = rng.integers(0, N + 9, Q).astype(np.int32)
+    kw = dict(E=2.0, w_v=0.5, tau_c=0.05, tau_v=1.0, delta=2, first_candidate=1, k=k)
+    print(f"N={N} Q={Q} k={k}", flush=True)
+    idx, score, count, _ = rv.retrieve_chunks(dev(bank), dev(query), dev(chunk), **kw)
+    at = np.r_[0, 1, rng.integers(0, Q, 40), Q - 1]
+    want_i, want_s, want_c = ORT.retrieve(bank, query[at], chunk[at], 2.0, 0.5, 0.05, 1.0, 2, 1, k)
+    assert np.array_equal(host(count)[at], want_c) and np.array_equal(host(idx)[at], want_i)
+    assert same_bits_f32(host(score)[at], want_s.astype(np.float32)).all()
