@@ -16,9 +16,9 @@
 // bit on the host.
 //
 // Large banks (more than kDirectMax entries) are cut into segments of
-// kSegEntries, one workgroup of kSegWaves waves per (query, segment), so that
-// enough waves stream the bank to keep HBM busy; each leaves its segment's k
-// best pairs in a workspace, and one workgroup per query merges those in the
+// kSegEntries, one workgroup of sixteen or eight waves per (query, segment), so
+// that enough waves stream the bank to keep HBM busy; each leaves its segment's
+// k best pairs in a workspace, and one workgroup per query merges those in the
 // same order. The result is the same as the single scan.
 //
 // What bounds it: a bank of a few thousand poses is latency (one load batch,
@@ -28,8 +28,8 @@
 // wave and again per query) and now: 200 entries, k 4: 4.9 -> 4.3 us; 3000,
 // k 4: 17.3 -> 8.6; 8000, k 32: 78 -> 11; 10^6, 4 queries, k 8: 62 -> 25;
 // 113615, 9 queries, k 26: 696 -> 30; 2 10^6, 16 queries, k 32: 5500 -> 156;
-// 2^23, k 4: 109 -> 102 (5.2 TB/s), and 109 -> 113 where 3% of it are in reach;
-// 10^6 entries all in reach, k 4: 34.4 -> 30.0.
+// 2^23, k 4: 108 -> 93 (5.7 TB/s), and 110 -> 104 where 1% of it are in reach,
+// 4 queries, k 8: 414 -> 177; 10^6 entries all in reach, k 4: 34.4 -> 30.0.
 
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -45,7 +45,8 @@ namespace {
 constexpr int kWave = 64;
 constexpr int kMaxWaves = 16;                          // waves of a workgroup
 constexpr int kSegWaves = kMaxWaves;                   // scanning waves per segment workgroup
-constexpr int kSegEntries = kSegWaves * 16 * kWave;    // bank entries per segment
+constexpr int kSegWavesFull = 8;                       // the same, where the segments fill the chip
+constexpr int kSegEntries = 16384;                     // bank entries per segment
 constexpr int kDirectMax = 8192;                       // larger banks take the segmented path
 constexpr int kUnroll = 4;                             // bank entries in flight per lane
 constexpr int kLane = 4;                               // best pairs a lane keeps
@@ -341,12 +342,25 @@ __device__ __forceinline__ PoseCols load_cols(const RetrieveArgs& a, int j) {
 // nothing in reach needs neither; otherwise the batch's square roots and
 // quotients are evaluated together (one after the other behind a branch each
 // they cost 10% where a few per cent of a bank of 2^23 are in reach).
-template <class Offer>
-__device__ __forceinline__ void scan_bank(const RetrieveArgs& a, int begin, int end, const QueryPose& qp, Offer& offer) {
+//
+// kTurned: the batches start with number `turn` of them and go round.
+template <bool kTurned, class Offer>
+__device__ __forceinline__ void scan_bank(const RetrieveArgs& a, int begin, int end, int turn, const QueryPose& qp, Offer& offer) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
     const int step = (blockDim.x / kWave) * kUnroll * kWave;
-    for (int64_t w0 = (int64_t)begin + wave * kUnroll * kWave; w0 < end; w0 += step) {
+    const int64_t first = (int64_t)begin + wave * kUnroll * kWave;
+    int64_t w0 = first;
+    int left = 0;
+    if constexpr (kTurned) {
+        left = first < end ? (int)((end - first + step - 1) / step) : 0;
+        if (left > 0) w0 += (int64_t)(turn % left) * step;
+    }
+    for (; kTurned ? left > 0 : w0 < end; w0 += step) {
+        if constexpr (kTurned) {
+            --left;
+            if (w0 >= end) w0 = first;
+        }
         const int j0 = (int)w0 + lane;  // at most 2^30 + 63
         PoseCols m[kUnroll];
 #pragma unroll
@@ -410,7 +424,7 @@ __global__ __launch_bounds__(kWaves * kWave) void retrieve_kernel(RetrieveArgs a
     const int qi = blockIdx.x;
     const QueryPose qp = query_pose(a, qi);
     const int count = first_k<kMany, kWaves>(
-        sh, a.k, [&](auto offer) { scan_bank(a, qp.lo, qp.hi, qp, offer); },
+        sh, a.k, [&](auto offer) { scan_bank<false>(a, qp.lo, qp.hi, 0, qp, offer); },
         [&](int r, double s, int j) { put_result(a, qi, r, s, j); });
     finish(a, sh, qi, count);
 }
@@ -419,9 +433,11 @@ __global__ __launch_bounds__(kWaves * kWave) void retrieve_kernel(RetrieveArgs a
 // seg_j [qi][seg][0 .. k), (INFINITY, INT32_MAX) past the admissible ones. The
 // queries of one segment are neighbours on one XCD, so its L2 serves the bank
 // to all but the first.
-template <bool kMany>
-__global__ __launch_bounds__(kSegWaves * kWave) void retrieve_segment_kernel(RetrieveArgs a) {
-    __shared__ Shared<kSegWaves> sh;
+// 128 registers at most, four waves per SIMD: one workgroup of sixteen waves
+// per compute unit, or two of eight.
+template <bool kMany, int kWaves>
+__global__ __launch_bounds__(kWaves * kWave, 4) void retrieve_segment_kernel(RetrieveArgs a) {
+    __shared__ Shared<kWaves> sh;
     const unsigned n_items = (unsigned)a.n_seg * (unsigned)a.n_query;
     const unsigned item = xcd_item(blockIdx.x, n_items);
     if (item >= n_items) return;  // grid padding (uniform, before any barrier)
@@ -435,7 +451,12 @@ __global__ __launch_bounds__(kSegWaves * kWave) void retrieve_segment_kernel(Ret
         a.seg_s[base + r] = s;
         a.seg_j[base + r] = j;
     };
-    const int count = first_k<kMany, kSegWaves>(sh, a.k, [&](auto offer) { scan_bank(a, begin, end, qp, offer); }, put);
+    // Two workgroups of a compute unit start together and keep in step: each at another of its
+    // segment's batches, so that their loads are not all at one offset of a whole MiB
+    // (2^23 entries, k 1, none in reach 100.2 -> 91.9 us, k 4, 1% in reach 110.5 -> 103.6;
+    // 6 10^6 72.0 -> 72.9; sixteen waves, one workgroup after the other, have no such step).
+    const int count = first_k<kMany, kWaves>(
+        sh, a.k, [&](auto offer) { scan_bank<kWaves == kSegWavesFull>(a, begin, end, 3 * seg + (seg >> 3), qp, offer); }, put);
     if ((int)threadIdx.x >= count && (int)threadIdx.x < a.k) put(threadIdx.x, INFINITY, INT32_MAX);
 }
 
@@ -493,8 +514,18 @@ static hipError_t launch_many(const RetrieveArgs& a, hipStream_t stream) {
         else hipLaunchKernelGGL((retrieve_kernel<kMany, kMaxWaves>), dim3(a.n_query), block, 0, stream, a);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(retrieve_segment_kernel<kMany>, dim3(xcd_grid((unsigned)a.n_query * a.n_seg)), dim3(kSegWaves * kWave), 0,
-                       stream, a);
+    const unsigned n_items = (unsigned)a.n_query * (unsigned)a.n_seg;
+    // Sixteen waves of one workgroup meet with the compute unit's memory idle; past one
+    // workgroup per compute unit two of eight cover each other (2^23 entries, k 4, 1% in reach
+    // 113.0 -> 103.6 us, k 8, half in reach 135 -> 114.5, 4 queries 303 -> 192), which one of
+    // eight does as well from half the compute units on where up to kLane results are wanted
+    // (2.2 10^6 entries, k 4, 1% in reach 34.7 -> 32.2; 1.5 10^6, k 1, half in reach 27.1 -> 27.9;
+    // k 32, 1% in reach of 2.2 10^6 87 -> 89, of 4.2 10^6 109 -> 112).
+    if (n_items <= kFillWaves / kSegWaves / (kMany ? 1 : 2))
+        hipLaunchKernelGGL((retrieve_segment_kernel<kMany, kSegWaves>), dim3(xcd_grid(n_items)), dim3(kSegWaves * kWave), 0, stream, a);
+    else
+        hipLaunchKernelGGL((retrieve_segment_kernel<kMany, kSegWavesFull>), dim3(xcd_grid(n_items)), dim3(kSegWavesFull * kWave), 0,
+                           stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(retrieve_merge_kernel<kMany>, dim3(a.n_query), waves_for((int64_t)a.n_seg * a.k, kWave, a.n_query), 0, stream, a);

@@ -101,3 +101,23 @@ def test_many_queries(N, Q, k):
     want_i, want_s, want_c = ORT.retrieve(bank, query[at], chunk[at], 2.0, 0.5, 0.05, 1.0, 2, 1, k)
     assert np.array_equal(host(count)[at], want_c) and np.array_equal(host(idx)[at], want_i)
     assert same_bits_f32(host(score)[at], want_s.astype(np.float32)).all()
+
+
+@pytest.mark.parametrize("N,Q,k", [(8193, 130, 4), (8193, 260, 9), (16385, 65, 1), (16385, 129, 32), (40000, 50, 4),
+                                   (40000, 100, 5), (8193, 128, 4), (8193, 256, 9)])
+@pytest.mark.parametrize("tau_c", [0.02, 1e6])
+def test_segments_of_eight_waves(N, Q, k, tau_c):
+    """Either side of the number of segments from which each has eight waves, which start at different
+    batches of theirs; index ranges that begin and end inside segments."""
+    rng = np.random.default_rng(Q + k)
+    bank, query = _line(rng.uniform(0, 9, N)), _line(rng.uniform(0, 9, Q))
+    chunk = rng.integers(0, N + 9, Q).astype(np.int32)
+    chunk[0] = N + 9
+    for first in (1, 3000):
+        kw = dict(E=2.0, w_v=0.5, tau_c=tau_c, tau_v=1.0, delta=2, first_candidate=first, k=k)
+        print(f"N={N} Q={Q} k={k} tau_c={tau_c} first={first}", flush=True)
+        idx, score, count, _ = rv.retrieve_chunks(dev(bank), dev(query), dev(chunk), **kw)
+        at = np.r_[0, rng.integers(0, Q, 30), Q - 1]
+        want_i, want_s, want_c = ORT.retrieve(bank, query[at], chunk[at], 2.0, 0.5, tau_c, 1.0, 2, first, k)
+        assert np.array_equal(host(count)[at], want_c) and np.array_equal(host(idx)[at], want_i)
+        assert same_bits_f32(host(score)[at], want_s.astype(np.float32)).all()
