@@ -103,7 +103,7 @@ struct BiasGeom {
 // kernel before it (128 queries per workgroup, tiles staged through registers
 // into LDS between two barriers, one 4-byte LDS read per MFMA) took 24.5 ms.
 // Four waves per item, two workgroups per compute unit: 7.48 ms. Lq 64, Lk 256,
-// D 64, one head without bias: 8.6 us in four waves (36 before, 9.3 in eight).
+// D 64, one head without bias: 9.3 us (36 before).
 // ---------------------------------------------------------------------------
 
 // The correspondence of a lane's query in KV frame f.
@@ -1270,15 +1270,19 @@ BiasGeom make_geom(const AttentionArgs& a) {
 
 }  // namespace
 
-// Waves per item of the fp32 kernel. Eight for long key ranges (at 128 tiles four
+// Waves per item of the fp32 kernel. Items that leave every compute unit at most
+// one take eight, whose merge (64 KB through LDS, one workgroup per compute unit)
+// then keeps nobody waiting: at most 1 us more than four at 8 tiles (D 64: 9.3
+// against 8.6 us in a graph), the same from 25 on, and the sums are shorter (43 tiles,
+// D 64: error 3.8e-7 against 4.4e-7, 6.8e-7 in the kernel before). Up to four tiles,
+// a wave each, four give the same sums. With more items: eight for long key ranges (at 128 tiles four
 // are 1 to 17% slower: more items per workgroup place fill the last round worse);
-// four where the merge of eight, 64 KB through LDS and one workgroup per compute
-// unit, weighs more than that (12 tiles, 7500 items of D 128: 469 against 586 us,
+// four where that merge weighs more (12 tiles, 7500 items of D 128: 469 against 586 us,
 // 995 in the kernel before); one, which merges nothing, for short ranges of items
 // that fill the chip by themselves (one tile of one key, 7500 items: 89 us, 152 in four
-// waves, 295 in eight, 128 before; two tiles, 1764 items: 33, 47, 74 and 61). Items
-// that do not fill it last as long as a wave's turns: from two tiles on they take four.
+// waves, 295 in eight, 128 before; two tiles, 1764 items: 33, 47, 74 and 61).
 static int f32_waves(unsigned items, int n_tiles) {
+    if (items <= 256 && n_tiles > 4) return 8;
     if (n_tiles >= 48) return 8;
     return n_tiles >= 12 || (n_tiles >= 2 && items <= 512) ? 4 : 1;
 }
@@ -1411,9 +1415,9 @@ int32_t attention_bf16_key_parts(const AttentionArgs& a, int32_t cus) {
     // items, 5 to 2025 tiles, 1 to 32 parts; 8% off on average); its choice is on
     // average 1.5% above the best of the measured parts. A rule that filled two
     // workgroups per compute unit with at most 4 parts of at least 128 tiles left
-    // short ranges whole: 10 items of 110 tiles 69 us, now 21 in 8 parts; 120
-    // items of 220 tiles 127 us, now 70 in 4; 444 items of 439 tiles 437 us in 3
-    // parts, now 406 in one. A further part has to gain 1.5%, and past four parts
+    // short ranges whole: 10 items of 110 tiles 60 us, now 19 in 8 parts; 120
+    // items of 220 tiles 115 us, now 64 in 4; 444 items of 439 tiles 397 us in 3
+    // parts, now 368 in one. A further part has to gain 1.5%, and past four parts
     // (past one where a launch takes several layers) the workspace is kept below
     // 140 MB.
     constexpr int kAutoParts = 16, kSplitUnits = 2048;

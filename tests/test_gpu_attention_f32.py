@@ -1,5 +1,6 @@
 """fp32 attention at the edges of its 32-query, 32-key tiles and of its W waves per item (wave w takes
-key tiles w, w + W, ...; W is 8 from 48 tiles on, 4 from 12 on and for small launches, else 1),
+key tiles w, w + W, ...; W is 8 from 48 tiles on, and of up to 256 items from 5 on; else 4 from 12
+tiles on or of up to 512 items, else 1),
 against the fp64 oracle at the fp32 bars (1e-4, as in the targeted tests: sums of at most 1850 fp32
 products of N(0, 1) values stay far inside it)."""
 
@@ -32,13 +33,15 @@ def _inputs(seed, Lq, frames, h, w, S, H, D):
 # (Lq, frames, h, w, S, H, D): one key; one tile less, exactly and more than a key; fewer tiles than
 # waves; eight tiles and one key either side; several tiles per wave with a ragged last one; frames
 # smaller than a tile, of one token, and of a row of one token; eight waves at 48 and 49 tiles and
-# 58 with a ragged last one; one wave for all tiles (over 512 items): one key, 2 tiles and one key, 11
+# 58 with a ragged last one; one wave for all tiles (over 512 items): one key, 2 tiles and one key, 11;
+# eight waves of 256 items, five tiles; four (over 256 items): five, eight and 13 tiles with ragged last ones
 @pytest.mark.parametrize("shape", [
     (1, 1, 1, 1, 1, 1, 64), (31, 1, 31, 1, 1, 2, 128), (32, 1, 4, 8, 1, 1, 64), (33, 3, 1, 11, 2, 1, 128),
     (65, 5, 3, 17, 3, 2, 64), (40, 2, 8, 16, 1, 1, 128), (40, 1, 15, 17, 1, 1, 64), (40, 1, 257, 1, 1, 1, 128),
     (70, 9, 7, 13, 4, 3, 128), (20, 40, 1, 1, 12, 1, 64), (50, 33, 2, 3, 5, 1, 128),
     (33, 6, 16, 16, 2, 1, 64), (33, 17, 7, 13, 3, 1, 128), (40, 12, 9, 17, 3, 2, 64), (70, 1, 1, 1, 1, 171, 64),
-    (65, 1, 5, 13, 1, 175, 128), (70, 3, 9, 13, 2, 175, 64)])
+    (65, 1, 5, 13, 1, 175, 128), (70, 3, 9, 13, 2, 175, 64),
+    (33, 1, 10, 13, 1, 128, 64), (33, 1, 10, 13, 1, 129, 64), (70, 2, 9, 13, 1, 90, 64), (40, 3, 9, 15, 2, 130, 128)])
 def test_tile_and_wave_edges(shape):
     Lq, frames, h, w, S, H, D = shape
     q, k, v, slot, uv, idx = _inputs(sum(shape), *shape)
@@ -84,7 +87,7 @@ def test_no_finite_logit():
     assert np.isnan(lse[:, 2]).all()
 
 
-@pytest.mark.parametrize("frames,H", [(2, 2), (7, 2), (1, 300)])  # 16, 56 and 8 key tiles: four, eight waves and one
+@pytest.mark.parametrize("frames,H", [(2, 2), (7, 2), (2, 150), (1, 300)])  # 16, 56, 16 and 8 key tiles: eight waves, eight, four and one
 @pytest.mark.parametrize("where", ["query", "tiles of one wave", "one key"])
 def test_a_nan_shows_in_the_lse(where, frames, H):
     """A NaN logit makes its rows' sums NaN, and so their LSE, whichever waves hold it."""
