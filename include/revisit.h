@@ -270,6 +270,8 @@ int reproject_correspondence(const float* tgt_depth, const float* tgt_c2w, const
  *               or make four such rounds and no 2 to 4 parts of 128 tiles or
  *               more do. The keys are then cut into as many parts as fit in it
  *               (one that is not 16-byte aligned counts as none).
+ *               Calls that may overlap in time (on two streams) must not share
+ *               a workspace, short key ranges included.
  */
 int biased_chunk_attention(const void* q, const void* k, const void* v, void* o,
                            float* lse, int32_t dtype,

@@ -44,8 +44,13 @@ def _ptr(t: Optional[torch.Tensor]):
     return t.data_ptr() if t is not None else None
 
 
+# not public names: without them the slower public ones
+_current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda index: torch.cuda.current_stream(index).cuda_stream)
+
+
 def _stream(device: torch.device):
-    return torch._C._cuda_getCurrentRawStream(device.index)
+    return _raw_stream(device.index)
 
 
 def _need(t: torch.Tensor, name: str, dtype: torch.dtype, shape: Optional[Sequence[int]] = None, device=None):
@@ -291,7 +296,7 @@ def biased_chunk_attention(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, kv
                                                   softmax_scale, lam, sigma, int(key_parts), _stream(dev))
         _lib.check("biased_chunk_attention_noalloc", st)
         return o, lse
-    if torch._C._cuda_getDevice() == dev.index:
+    if _current_device() == dev.index:
         nbytes = attention_workspace_size(q.dtype, Lq, Lk, H, D, key_parts)
     else:
         with torch.cuda.device(dev):
