@@ -343,8 +343,12 @@ __device__ __forceinline__ PoseCols load_cols(const RetrieveArgs& a, int j) {
 // quotients are evaluated together (one after the other behind a branch each
 // they cost 10% where a few per cent of a bank of 2^23 are in reach).
 //
+// kEach: one after the other all the same, for workgroups of one wave, few of
+// whose banks have entries in reach in all four (53 entries, k 1: 4.0 -> 3.8 us; 130
+// entries, 2210 queries, k 3: 8.1 -> 7.8).
+//
 // kTurned: the batches start with number `turn` of them and go round.
-template <bool kTurned, class Offer>
+template <bool kTurned, bool kEach, class Offer>
 __device__ __forceinline__ void scan_bank(const RetrieveArgs& a, int begin, int end, int turn, const QueryPose& qp, Offer& offer) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
@@ -378,16 +382,27 @@ __device__ __forceinline__ void scan_bank(const RetrieveArgs& a, int begin, int 
             any = any || near[u];
         }
         if (!__any(any)) continue;
-        double s[kUnroll];
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        auto score = [&](int u, double& s) {
             const double d = sqrt(x[u]) / a.E;
-            s[u] = d + a.w_v * (1.0 - al[u]);
+            s = d + a.w_v * (1.0 - al[u]);
             near[u] = near[u] && d <= a.tau_c;
-        }
+        };
+        if constexpr (kEach) {
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            if (near[u]) offer(s[u], j0 + u * kWave);
+            for (int u = 0; u < kUnroll; ++u) {
+                if (!__any(near[u])) continue;
+                double s;
+                score(u, s);
+                if (near[u]) offer(s, j0 + u * kWave);
+            }
+        } else {
+            double s[kUnroll];
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) score(u, s[u]);
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) {
+                if (near[u]) offer(s[u], j0 + u * kWave);
+            }
         }
     }
 }
@@ -424,7 +439,7 @@ __global__ __launch_bounds__(kWaves * kWave) void retrieve_kernel(RetrieveArgs a
     const int qi = blockIdx.x;
     const QueryPose qp = query_pose(a, qi);
     const int count = first_k<kMany, kWaves>(
-        sh, a.k, [&](auto offer) { scan_bank<false>(a, qp.lo, qp.hi, 0, qp, offer); },
+        sh, a.k, [&](auto offer) { scan_bank<false, kWaves == 1>(a, qp.lo, qp.hi, 0, qp, offer); },
         [&](int r, double s, int j) { put_result(a, qi, r, s, j); });
     finish(a, sh, qi, count);
 }
@@ -456,7 +471,7 @@ __global__ __launch_bounds__(kWaves * kWave, 4) void retrieve_segment_kernel(Ret
     // (2^23 entries, k 1, none in reach 100.2 -> 91.9 us, k 4, 1% in reach 110.5 -> 103.6;
     // 6 10^6 72.0 -> 72.9; sixteen waves, one workgroup after the other, have no such step).
     const int count = first_k<kMany, kWaves>(
-        sh, a.k, [&](auto offer) { scan_bank<kWaves == kSegWavesFull>(a, begin, end, 3 * seg + (seg >> 3), qp, offer); }, put);
+        sh, a.k, [&](auto offer) { scan_bank<kWaves == kSegWavesFull, false>(a, begin, end, 3 * seg + (seg >> 3), qp, offer); }, put);
     if ((int)threadIdx.x >= count && (int)threadIdx.x < a.k) put(threadIdx.x, INFINITY, INT32_MAX);
 }
 
