@@ -533,10 +533,11 @@ static hipError_t launch_many(const RetrieveArgs& a, hipStream_t stream) {
     // Sixteen waves of one workgroup meet with the compute unit's memory idle; past one
     // workgroup per compute unit two of eight cover each other (2^23 entries, k 4, 1% in reach
     // 113.0 -> 103.6 us, k 8, half in reach 135 -> 114.5, 4 queries 303 -> 192), which one of
-    // eight does as well from half the compute units on where up to kLane results are wanted
+    // eight does as well from half the compute units on for one query of up to kLane results
     // (2.2 10^6 entries, k 4, 1% in reach 34.7 -> 32.2; 1.5 10^6, k 1, half in reach 27.1 -> 27.9;
-    // k 32, 1% in reach of 2.2 10^6 87 -> 89, of 4.2 10^6 109 -> 112).
-    if (n_items <= kFillWaves / kSegWaves / (kMany ? 1 : 2))
+    // k 32, 1% in reach of 2.2 10^6 87 -> 89, of 4.2 10^6 109 -> 112; several queries read the
+    // bank from the L2: 67000, 33 queries, k 3, all in reach 27.0 -> 28.4).
+    if (n_items <= kFillWaves / kSegWaves / (!kMany && a.n_query == 1 ? 2 : 1))
         hipLaunchKernelGGL((retrieve_segment_kernel<kMany, kSegWaves>), dim3(xcd_grid(n_items)), dim3(kSegWaves * kWave), 0, stream, a);
     else
         hipLaunchKernelGGL((retrieve_segment_kernel<kMany, kSegWavesFull>), dim3(xcd_grid(n_items)), dim3(kSegWavesFull * kWave), 0,

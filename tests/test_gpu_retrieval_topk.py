@@ -103,8 +103,8 @@ def test_many_queries(N, Q, k):
     assert same_bits_f32(host(score)[at], want_s.astype(np.float32)).all()
 
 
-@pytest.mark.parametrize("N,Q,k", [(8193, 130, 4), (8193, 260, 9), (16385, 65, 1), (16385, 129, 32), (40000, 50, 4),
-                                   (40000, 100, 5), (8193, 128, 4), (8193, 256, 9)])
+@pytest.mark.parametrize("N,Q,k", [(8193, 256, 4), (8193, 257, 4), (8193, 260, 9), (16385, 129, 1), (16385, 129, 32),
+                                   (40000, 90, 4), (40000, 100, 5), (8193, 256, 9)])
 @pytest.mark.parametrize("tau_c", [0.02, 1e6])
 def test_segments_of_eight_waves(N, Q, k, tau_c):
     """Either side of the number of segments from which each has eight waves, which start at different
@@ -121,3 +121,14 @@ def test_segments_of_eight_waves(N, Q, k, tau_c):
         want_i, want_s, want_c = ORT.retrieve(bank, query[at], chunk[at], 2.0, 0.5, tau_c, 1.0, 2, first, k)
         assert np.array_equal(host(count)[at], want_c) and np.array_equal(host(idx)[at], want_i)
         assert same_bits_f32(host(score)[at], want_s.astype(np.float32)).all()
+
+
+@pytest.mark.parametrize("N", [128 * 16384, 128 * 16384 + 1, 131 * 16384 - 77])
+def test_one_query_of_many_segments(N):
+    """One query's segments either side of half the compute units, some in reach in many of them."""
+    rng = np.random.default_rng(N)
+    x = rng.uniform(1, 9, N).astype(np.float32)
+    x[rng.integers(0, N, 500)] = np.float32(0.125) + rng.integers(0, 8, 500).astype(np.float32) / 64
+    for k in (1, 4, 9):
+        for first, chunk in ((1, N + 9), (1234567, 2000000)):
+            _check(_line(x), _line(np.zeros(1)), np.array([chunk], np.int32), k, E=1.0, tau_c=0.2, first=first)
