@@ -578,7 +578,7 @@ __device__ __forceinline__ void rotate_pair(const ReprojectArgs& a, const double
 // launches of few sources whose frames end in the middle of a line: the launch
 // above writes past the L2, one source after the other, and a line cut
 // between two frames costs it twice (1024 problems of 30 x 52 and 6 sources
-// 89 -> 78 us, 345 MB; 45 x 79 and 6 sources, 33 million pairs, 1.64 times as
+// 89 -> 79 us, 345 MB; 45 x 79 and 6 sources, 33 million pairs, 1.64 times as
 // fast). Where frames end on lines it is the faster one (the same pairs of
 // 45 x 80: 1.07 times, of 128 x 128: 1.35 times) but for one or two sources, whose
 // homographies its blocks wait for (1.22 to 1.8 times), and three (1.03 to 1.16
