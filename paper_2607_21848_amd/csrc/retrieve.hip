@@ -22,7 +22,8 @@
 // same order. The result is the same as the single scan.
 //
 // What bounds it: a bank of a few thousand poses is latency (one load batch,
-// the gates, five barriers), a large one the stream of its 64-byte poses.
+// the gates, five barriers where one scan settles it), a large one the stream of
+// its 64-byte poses.
 // Measured per call on the device (a captured graph of calls), before (one wave per query scanning in
 // turn, sorted lists of up to 32 pairs in registers, k butterfly rounds per
 // wave and again per query) and now: 200 entries, k 4: 4.9 -> 4.3 us; 3000,
