@@ -455,8 +455,9 @@ template <bool kMany, int kWaves>
 __global__ __launch_bounds__(kWaves * kWave, 4) void retrieve_segment_kernel(RetrieveArgs a) {
     __shared__ Shared<kWaves> sh;
     const unsigned n_items = (unsigned)a.n_seg * (unsigned)a.n_query;
-    const unsigned item = xcd_item(blockIdx.x, n_items);
-    if (item >= n_items) return;  // grid padding (uniform, before any barrier)
+    const unsigned block = row_block();
+    const unsigned item = xcd_item(block, n_items);
+    if (block >= xcd_grid(n_items) || item >= n_items) return;  // grid padding (uniform, before any barrier)
     const int seg = (int)(item / (unsigned)a.n_query);
     const int qi = (int)(item - (unsigned)seg * (unsigned)a.n_query);
     const QueryPose qp = query_pose(a, qi);
@@ -541,8 +542,8 @@ static hipError_t launch_many(const RetrieveArgs& a, hipStream_t stream) {
     if (n_items <= kFillWaves / kSegWaves / (!kMany && a.n_query == 1 ? 2 : 1))
         hipLaunchKernelGGL((retrieve_segment_kernel<kMany, kSegWaves>), dim3(xcd_grid(n_items)), dim3(kSegWaves * kWave), 0, stream, a);
     else
-        hipLaunchKernelGGL((retrieve_segment_kernel<kMany, kSegWavesFull>), dim3(xcd_grid(n_items)), dim3(kSegWavesFull * kWave), 0,
-                           stream, a);
+        hipLaunchKernelGGL((retrieve_segment_kernel<kMany, kSegWavesFull>), grid_rows(xcd_grid(n_items)), dim3(kSegWavesFull * kWave),
+                           0, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(retrieve_merge_kernel<kMany>, dim3(a.n_query), waves_for((int64_t)a.n_seg * a.k, kWave, a.n_query), 0, stream, a);

@@ -30,10 +30,10 @@ def _poses(x, y):
     return m
 
 
-@pytest.mark.parametrize("k", [1, 5])
-def test_retrieval_of_many_queries(k):
-    """2^22 + 5 queries over 4000 entries, which sixteen waves a query would scan."""
-    N, Q = 4000, (1 << 22) + 5
+@pytest.mark.parametrize("N,Q,k", [(4000, (1 << 22) + 5, 1), (4000, (1 << 22) + 5, 5), (8200, (1 << 23) + 5, 1)])
+def test_retrieval_of_many_queries(N, Q, k):
+    """2^22 + 5 queries over 4000 entries, which sixteen waves a query would scan; 2^23 + 5 segments of
+    eight waves."""
     g = torch.Generator(device="cuda").manual_seed(k)
     r = lambda n: 20 * torch.rand(n, generator=g, device="cuda")  # noqa: E731
     bank, query = _poses(r(N), r(N)), _poses(r(Q), r(Q))
@@ -41,7 +41,7 @@ def test_retrieval_of_many_queries(k):
     kw = dict(E=20.0, w_v=0.5, tau_c=0.02, tau_v=1.0, delta=3, first_candidate=1, k=k)
     print(f"N={N} Q={Q} k={k}", flush=True)
     idx, score, count, _ = rv.retrieve_chunks(bank, query, chunk, **kw)
-    at = torch.tensor([0, 1, 4095, 1 << 20, (1 << 22) - 1, 1 << 22, Q - 1], device="cuda")
+    at = torch.tensor([0, 1, 4095, 1 << 20, (1 << 22) - 1, 1 << 22, Q - 6, Q - 5, Q - 1], device="cuda")
     want_i, want_s, want_c = ORT.retrieve(host(bank), host(query[at]), host(chunk[at]), 20.0, 0.5, 0.02, 1.0, 3, 1, k)
     assert want_c.max() > 0
     assert np.array_equal(host(idx[at]), want_i) and np.array_equal(host(count[at]), want_c)
